@@ -8,11 +8,13 @@ import os
 import subprocess
 import sys
 import time
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsnn.so")
-SOURCES = ["kernels_build.hip", "kernels_step.hip", "kernels_rec.hip", "kernels_stdp.hip", "snn_api.cpp", "snn_server.cpp"]
+SOURCES = ["kernels_adex_beta.hip", "kernels_adex_exp.hip", "kernels_step.hip", "kernels_build.hip", "kernels_rec.hip",
+           "kernels_stdp.hip", "snn_api.cpp", "snn_server.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("SNN_OFFLOAD_ARCH", "gfx950")
 
@@ -44,11 +46,9 @@ def build(verbose: bool = True) -> str:
     t0 = time.time()
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
-    for s in SOURCES:
-        obj = os.path.join(objdir, os.path.splitext(s)[0] + ".o")
-        _compile(os.path.join(CSRC, s), obj)
-        objs.append(obj)
+    objs = [os.path.join(objdir, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+    with ThreadPoolExecutor(max_workers=4) as ex:
+        list(ex.map(_compile, [os.path.join(CSRC, s) for s in SOURCES], objs))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
