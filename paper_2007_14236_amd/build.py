@@ -13,8 +13,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsnn.so")
-SOURCES = ["kernels_adex_beta.hip", "kernels_adex_exp.hip", "kernels_step.hip", "kernels_build.hip", "kernels_rec.hip",
-           "kernels_stdp.hip", "snn_api.cpp", "snn_server.cpp"]
+SOURCES = ["kernels_adex_beta.hip", "kernels_adex_beta_plastic.hip", "kernels_adex_exp.hip",
+           "kernels_adex_exp_plastic.hip", "kernels_step.hip", "kernels_build.hip", "kernels_rec.hip", "kernels_stdp.hip",
+           "snn_api.cpp", "snn_server.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("SNN_OFFLOAD_ARCH", "gfx950")
 
@@ -47,7 +48,7 @@ def build(verbose: bool = True) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     objs = [os.path.join(objdir, os.path.splitext(s)[0] + ".o") for s in SOURCES]
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         list(ex.map(_compile, [os.path.join(CSRC, s) for s in SOURCES], objs))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs

@@ -50,12 +50,16 @@ hipError_t launch_runs(bool fill, const uint64_t* grp_off, uint64_t n_groups, co
 // the kernel's own dispatch.
 hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start = nullptr,
                        hipEvent_t stop = nullptr);
-// The step kernels of networks with AdEx neurons, exponential ports only or
-// with beta ports (launch_step picks one).
+// The step kernels of networks with AdEx neurons: exponential ports only or
+// with beta ports, without or with plastic synapses (launch_step picks one).
 void launch_adex_exp(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,
                      bool lif);
 void launch_adex_beta(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,
                       bool lif);
+void launch_adex_exp_plastic(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop,
+                             uint32_t rel, bool lif);
+void launch_adex_beta_plastic(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop,
+                              uint32_t rel, bool lif);
 hipError_t launch_advance(Ctrl* ctrl, uint32_t steps, hipStream_t s);
 // Binned delivery: add the pending bin entries of input buffer `buf` on `port`
 // for gids [first, first+n) to out[0..n) (device int64).

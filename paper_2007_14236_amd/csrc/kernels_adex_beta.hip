@@ -5,7 +5,7 @@ namespace snn {
 
 void launch_adex_beta(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,
                     bool lif) {
-  launch_adex<2>(nd, grid, s, start, stop, rel, lif);
+  launch_adex<2, false>(nd, grid, s, start, stop, rel, lif);
 }
 
 }  // namespace snn

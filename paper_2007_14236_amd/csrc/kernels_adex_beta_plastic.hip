@@ -1,0 +1,11 @@
+// kernels_adex_beta_plastic.hip -- step kernels of networks with AdEx neurons (beta ports, plastic synapses).
+#include "step_dev.h"
+
+namespace snn {
+
+void launch_adex_beta_plastic(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,
+                    bool lif) {
+  launch_adex<2, true>(nd, grid, s, start, stop, rel, lif);
+}
+
+}  // namespace snn

@@ -29,7 +29,9 @@ __device__ __forceinline__ int64_t table_at(const NetDev& nd, uint64_t off, uint
   return d < len ? nd.stdp_F[off + d] : 0;
 }
 
+// rule of plastic synapse j: with a single rule no load stands before it
 __device__ __forceinline__ const StdpRule& rule_of(const NetDev& nd, uint64_t j) {
+  if (nd.n_rules == 1) return nd.rules[0];
   const uint32_t cls = nd.payload[j] & ((1u << nd.cls_bits) - 1u);
   return nd.rules[nd.cls_rule[cls] - 1];
 }
@@ -51,7 +53,9 @@ __device__ __forceinline__ int64_t depress(const NetDev& nd, const StdpRule& r, 
 // synapse is potentiated, and, if it also receives a spike at step n + 1,
 // depressed at distance 1.  All lanes then take the arrivals of step n + 1
 // onto targets that did not fire at step n.  The two sets of synapses are
-// disjoint, and each synapse is one lane's, so no update races.
+// disjoint, and each synapse is one lane's, so no update races.  Bound by its
+// chain of dependent loads: an arrival carries its target, so that the
+// synapse's weight and the target's latest spike load side by side.
 __global__ void __launch_bounds__(kB) k_stdp(NetDev nd, uint32_t rel) {
   const uint64_t n = nd.ctrl->step_base + rel;
   const uint32_t slot = (uint32_t)(n % nd.R);
@@ -86,11 +90,12 @@ __global__ void __launch_bounds__(kB) k_stdp(NetDev nd, uint32_t rel) {
   const uint32_t na = nd.arr_cnt[b1];
   const uint64_t* list = nd.arr_list + (size_t)b1 * nd.n_plastic;
   for (uint64_t a = (uint64_t)blockIdx.x * kB + threadIdx.x; a < na; a += (uint64_t)gridDim.x * kB) {
-    const uint64_t j = list[a];
-    const uint32_t t = nd.payload[j] >> nd.cls_bits;
-    const uint32_t lpost = nd.last_post[t];
+    const uint64_t e = list[a], j = e & ((1ull << kArrTgtShift) - 1ull);
+    const int32_t w = nd.pw[j];  // beside the load of the target's latest spike
+    const uint32_t m = nd.arr_m[j];
+    const uint32_t lpost = nd.last_post[e >> kArrTgtShift];
     if (lpost == (uint32_t)(n + 1)) continue;  // fired at step n: done with its spike above
-    if (lpost) nd.pw[j] = (int32_t)depress(nd, rule_of(nd, j), nd.pw[j], n + 2 - (uint64_t)lpost, nd.arr_m[j]);
+    if (lpost) nd.pw[j] = (int32_t)depress(nd, rule_of(nd, j), w, n + 2 - (uint64_t)lpost, m);
     nd.last_pre[j] = (uint32_t)(n + 2);
     nd.arr_m[j] = 0;
   }

@@ -46,17 +46,18 @@ __global__ void __launch_bounds__(kB) k_pending_input(NetDev nd, uint32_t buf, u
 hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 blk(kB), grid((nd.n_tiles ? nd.n_tiles : nd.nblk_upd) + nd.sel_grid);
   const bool lif = nd.pad0 & 1u, adex = nd.pad0 & 2u, beta = nd.pad0 & 4u;
-  if (adex) {
-    if (beta) launch_adex_beta(nd, grid, s, start, stop, rel, lif);
-    else launch_adex_exp(nd, grid, s, start, stop, rel, lif);
+  const bool plastic = nd.n_rules != 0;
+  if (adex || (nd.n_tiles && !nd.tile_win)) {  // or a tile overlaps more populations than its LDS window holds
+    auto f = beta ? (plastic ? launch_adex_beta_plastic : launch_adex_beta)
+                  : (plastic ? launch_adex_exp_plastic : launch_adex_exp);
+    f(nd, grid, s, start, stop, rel, lif);
   } else if (!nd.n_tiles) {
-    launch(k_step<true, 0, 1>, grid, blk, s, start, stop, nd, rel);
-  } else if (!nd.tile_win) {  // a tile overlaps more populations than its LDS window holds
-    launch_adex_exp(nd, grid, s, start, stop, rel, true);
+    launch(plastic ? k_step<true, 0, 1, true> : k_step<true, 0, 1, false>, grid, blk, s, start, stop, nd, rel);
   } else if (nd.tile_runs) {
     launch(k_step_binned_runs<true, 0, 1>, grid, blk, s, start, stop, nd, rel);
   } else {
-    launch(k_step_binned<true, 0, 1>, grid, blk, s, start, stop, nd, rel);
+    launch(plastic ? k_step_binned<true, 0, 1, true> : k_step_binned<true, 0, 1, false>, grid, blk, s, start, stop, nd,
+           rel);
   }
   return hipGetLastError();
 }

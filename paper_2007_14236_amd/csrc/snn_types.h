@@ -51,6 +51,7 @@ constexpr int kRunLenBits = 22;                  // tile run descriptor: tile <<
 constexpr uint64_t kRunMaxGroup = 1ull << 20;     // tile runs only for groups below this size
 constexpr uint32_t kNoAllocInputMax = 1u << 18;  // neurons per call of the allocation-free input readback
 constexpr int kMaxDevices = 64;
+constexpr int kArrTgtShift = 36;     // arrival list entry: CSR position | target << 36 (at most 2^35 synapses)
 constexpr int kTagConn = 1;
 constexpr int kTagPoisson = 2;
 
@@ -194,7 +195,7 @@ struct NetDev {
   // arrival (0: none) and the multiplicity arriving at the next step; per
   // neuron the step + 1 of its latest spike; the plastic synapses onto each
   // target, tidx[tptr[t] .. tptr[t+1]); the plastic synapses an arrival step
-  // delivers to, arr_list[step & 1][0 .. arr_cnt[step & 1]).
+  // delivers to, arr_list[step & 1][0 .. arr_cnt[step & 1]) (with their targets).
   uint32_t n_rules, pad1;
   uint64_t n_plastic;
   const StdpRule* rules;

@@ -578,15 +578,42 @@ __device__ __forceinline__ uint32_t st_advance(const uint32_t* st, uint32_t n, u
 
 constexpr int kUnroll = 4;  // events per lane and round of a flat scan
 
-// A spike of multiplicity mult reaching plastic synapse j (CSR position) at
-// the step whose input buffer is buf (the arrival step's parity): its weight
-// as it is now, times mult, is the input; the arrival is recorded for the
-// plasticity kernel of this step (a synapse receives at most one spike per
-// step, so the list never holds more than the plastic synapses).
-__device__ __forceinline__ int64_t plastic_arrival(const NetDev& nd, uint64_t j, uint32_t mult, uint32_t buf) {
+// Places in the arrival list for a wave's plastic events of one round: lane
+// event q is one iff is[q]; its place is at[q].  One atomic on the list's
+// counter per wave and round: with an atomic per event, all on one address, a
+// step with 8,000 plastic arrivals (4,001 neurons, 1.6 10^6 synapses) took
+// 121 us with its plasticity kernel; now 19 us.  Lanes that have left the
+// caller's loop take no part.
+template <int Q>
+__device__ __forceinline__ void arrival_places(const NetDev& nd, uint32_t buf, const bool* is, uint32_t* at) {
+  const uint64_t here = __ballot(true), below = lanemask_lt();
+  uint32_t total = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint64_t m = __ballot(is[q]);
+    at[q] = total + (uint32_t)__popcll(m & below);
+    total += (uint32_t)__popcll(m);
+  }
+  if (total == 0) return;  // wave-uniform
+  const int leader = __ffsll((unsigned long long)here) - 1;
+  uint32_t base = 0;
+  if ((int)(threadIdx.x & 63) == leader)
+    base = __hip_atomic_fetch_add(&nd.arr_cnt[buf], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  base = __shfl(base, leader, 64);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) at[q] += base;
+}
+
+// A spike of multiplicity mult reaching plastic synapse j (CSR position) of
+// target tgt at the step whose input buffer is buf (the arrival step's
+// parity): its weight as it is now, times mult, is the input; the arrival is
+// recorded at place k of the list for the plasticity kernel of this step (a
+// synapse receives at most one spike per step, so the list never holds more
+// than the plastic synapses).
+__device__ __forceinline__ int64_t plastic_arrival(const NetDev& nd, uint64_t j, uint32_t tgt, uint32_t mult,
+                                                   uint32_t buf, uint32_t k) {
   nd.arr_m[j] = (uint8_t)mult;
-  const uint32_t k = __hip_atomic_fetch_add(&nd.arr_cnt[buf], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  nd.arr_list[(size_t)buf * nd.n_plastic + k] = j;
+  nd.arr_list[(size_t)buf * nd.n_plastic + k] = j | ((uint64_t)tgt << kArrTgtShift);
   return (int64_t)nd.pw[j] * (int64_t)mult;
 }
 
@@ -613,16 +640,24 @@ __device__ __forceinline__ void sel_gather(const NetDev& nd, const SelLds& sh, u
 // int64 input of its (target, port) in the input buffer of the pair's arrival
 // step with a device-scope atomic.  Called by the whole block after a barrier; returns
 // the events delivered and resets the chunk.
+template <bool kPl>
 __device__ uint64_t dlv_flush(const NetDev& nd, DirectLds& sh, uint32_t /*buf: per pair*/) {
   const uint32_t np = sh.npair;
   const uint64_t ev = sel_scan(sh);
   const size_t bstride = (size_t)nd.N * nd.P;
   const uint32_t cls_bits = nd.cls_bits, cls_mask = (1u << cls_bits) - 1u, P = nd.P;
-  const bool plastic = nd.n_rules != 0;
+  const bool plastic = kPl && nd.n_rules != 0;
   uint32_t lo = 0;
   for (uint64_t e0 = threadIdx.x; e0 < ev; e0 += kUnroll * kB) {  // independent events per lane and round
-    uint32_t r[kUnroll], pl[kUnroll];
+    uint32_t r[kUnroll], pl[kUnroll], at[kUnroll];
+    bool is_pl[kUnroll];
     sel_gather(nd, sh, np, ev, e0, lo, r, pl);
+    if (plastic) {  // every pair of a chunk arrives at the same step
+#pragma unroll
+      for (int q = 0; q < kUnroll; ++q)
+        is_pl[q] = e0 + (uint64_t)q * kB < ev && nd.cls_rule[pl[q] & cls_mask] != 0;
+      arrival_places<kUnroll>(nd, sh.p_buf[r[0]], is_pl, at);
+    }
 #pragma unroll
     for (int q = 0; q < kUnroll; ++q) {
       const uint64_t e = e0 + (uint64_t)q * kB;
@@ -630,8 +665,9 @@ __device__ uint64_t dlv_flush(const NetDev& nd, DirectLds& sh, uint32_t /*buf: p
       const uint32_t cls = pl[q] & cls_mask;
       const bool in_lds = cls < kClsLds;
       int64_t v;
-      if (plastic && nd.cls_rule[cls])
-        v = plastic_arrival(nd, sh.p_off[r[q]] + (e - sh.p_st[r[q]]), sh.p_mult[r[q]], sh.p_buf[r[q]]);
+      if (plastic && is_pl[q])
+        v = plastic_arrival(nd, sh.p_off[r[q]] + (e - sh.p_st[r[q]]), pl[q] >> cls_bits, sh.p_mult[r[q]],
+                            sh.p_buf[r[q]], at[q]);
       else
         v = (in_lds ? sh.wq[cls] : nd.cls_wq[cls]) * (int64_t)sh.p_mult[r[q]];
       const uint32_t port = in_lds ? sh.wp[cls] : nd.cls_port[cls];
@@ -662,8 +698,8 @@ __device__ __forceinline__ void bin_spill(const NetDev& nd, uint32_t buf, uint32
 // plasticity kernel changes it before the tile sums its bin), so the event
 // goes to the tile's spill accumulator, like an event that found its bin full.
 __device__ __forceinline__ void bin_plastic(const NetDev& nd, uint32_t buf, uint64_t j, uint32_t tgt, uint32_t cls,
-                                            uint32_t mult, uint32_t tile) {
-  const int64_t v = plastic_arrival(nd, j, mult, buf);
+                                            uint32_t mult, uint32_t tile, uint32_t k) {
+  const int64_t v = plastic_arrival(nd, j, tgt, mult, buf, k);
   __hip_atomic_fetch_add((unsigned long long*)&nd.acc[((size_t)buf * nd.N + tgt) * nd.P + nd.cls_port[cls]],
                          (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   nd.ovf_flag[(size_t)buf * nd.n_tiles + tile] = 1u;
@@ -714,11 +750,12 @@ __device__ __forceinline__ void lane_gather(const NetDev& nd, const BinLds& sh, 
 // atomic per tile reserves its range, then the chunk's synapses are written
 // (as in the count pass, kLaneRun consecutive ones per lane), spills and
 // plastic synapses aside.  Resets the chunk; returns ev.
+template <bool kPl>
 __device__ __forceinline__ uint64_t bin_write(const NetDev& nd, BinLds& sh, uint32_t buf, uint32_t np, uint64_t ev,
                                               uint32_t csh, bool bad) {
   const uint32_t cls_bits = nd.cls_bits, cls_mask = (1u << cls_bits) - 1u;
   const uint32_t tsh = nd.tile_shift, lmask = (1u << tsh) - 1u, ntl = nd.n_tiles;
-  const bool plastic = nd.n_rules != 0;
+  const bool plastic = kPl && nd.n_rules != 0;
   constexpr uint32_t kNone = 0xffffffffu;
   const uint64_t step = (uint64_t)kB * kLaneRun;
   __syncthreads();
@@ -746,15 +783,23 @@ __device__ __forceinline__ uint64_t bin_write(const NetDev& nd, BinLds& sh, uint
       uint32_t t = kNone;
       if (e0 + q < ev) {
         t = (pl[q] >> cls_bits) >> tsh;
-        if (t >= ntl) {
-          t = kNone;
-        } else if (plastic && nd.cls_rule[pl[q] & cls_mask]) {
-          bin_plastic(nd, buf, sh.p_off[r[q]] + (e0 + q - sh.p_st[r[q]]), pl[q] >> cls_bits, pl[q] & cls_mask,
-                      sh.p_mult[r[q]], t);
-          t = kNone;
-        }
+        if (t >= ntl) t = kNone;
       }
       tt[q] = t;
+    }
+    if (plastic) {
+      uint32_t at[kLaneRun];
+      bool is_pl[kLaneRun];
+#pragma unroll
+      for (int q = 0; q < kLaneRun; ++q) is_pl[q] = tt[q] != kNone && nd.cls_rule[pl[q] & cls_mask] != 0;
+      arrival_places<kLaneRun>(nd, buf, is_pl, at);
+#pragma unroll
+      for (int q = 0; q < kLaneRun; ++q) {
+        if (!is_pl[q]) continue;
+        bin_plastic(nd, buf, sh.p_off[r[q]] + (e0 + q - sh.p_st[r[q]]), pl[q] >> cls_bits, pl[q] & cls_mask,
+                    sh.p_mult[r[q]], tt[q], at[q]);
+        tt[q] = kNone;
+      }
     }
     // a run of consecutive events onto one tile: one LDS atomic, consecutive slots
 #pragma unroll
@@ -804,6 +849,7 @@ __device__ __forceinline__ uint64_t bin_write(const NetDev& nd, BinLds& sh, uint
 // a coarse index of the chunk's events), and a run of them onto one tile
 // takes one LDS atomic and consecutive entries.  Called by the whole block
 // after a barrier; returns the events delivered and resets the chunk.
+template <bool kPl>
 __device__ uint64_t dlv_flush(const NetDev& nd, BinLds& sh, uint32_t buf) {
   // every pair of a binned chunk arrives at the same step (buffer buf)
   const uint32_t np = sh.npair;
@@ -813,7 +859,7 @@ __device__ uint64_t dlv_flush(const NetDev& nd, BinLds& sh, uint32_t buf) {
   // below 32 (their sum can exceed 31 when a tile is wider than the gid range)
   const uint32_t cls_bits = nd.cls_bits, cls_mask = (1u << cls_bits) - 1u;
   const uint32_t tsh = nd.tile_shift, ntl = nd.n_tiles;
-  const bool plastic = nd.n_rules != 0;
+  const bool plastic = kPl && nd.n_rules != 0;
   constexpr uint32_t kNone = 0xffffffffu;
   bool bad = false;
   const uint64_t step = (uint64_t)kB * kLaneRun;
@@ -840,13 +886,15 @@ __device__ uint64_t dlv_flush(const NetDev& nd, BinLds& sh, uint32_t buf) {
     }
     if (k) atomicAdd(&sh.tcnt[tp], k);
   }
-  return bin_write(nd, sh, buf, np, ev, csh, bad);
+  return bin_write<kPl>(nd, sh, buf, np, ev, csh, bad);
 }
 
 // the same with the count pass over the chunk's tile runs (one 4-byte
 // descriptor per run instead of every synapse word: networks whose groups put
 // many synapses on each tile they touch, without plastic synapses)
+template <bool kPl>
 __device__ __forceinline__ uint64_t dlv_flush(const NetDev& nd, BinRunLds& sh, uint32_t buf) {
+  static_assert(!kPl, "tile runs are built only where no synapse is plastic");
   const uint32_t np = sh.npair;
   const uint64_t ev = sel_scan(sh);
   const uint32_t csh = build_cidx(sh, np, ev);
@@ -880,7 +928,7 @@ __device__ __forceinline__ uint64_t dlv_flush(const NetDev& nd, BinRunLds& sh, u
     else bad = true;
   }
   __syncthreads();
-  return bin_write(nd, sh, buf, np, ev, csh, bad);
+  return bin_write<kPl>(nd, sh, buf, np, ev, csh, bad);
 }
 
 // Synaptic state of AdEx neuron i into y[2..] with the step's input x (nS)
@@ -1094,7 +1142,7 @@ __device__ __forceinline__ void emit_spike(const NetDev& nd, uint64_t n, uint64_
 // counter (wave ballot + lane prefix), their raster entries and records are
 // written here, and their delay-1 groups are delivered at once by the
 // block's flat scan into the buffer of step n + 1.
-template <bool kLif, int kAd, int P>
+template <bool kLif, int kAd, int P, bool kPl>
 __device__ void update_block(const NetDev& nd, uint64_t n, uint32_t blk, UpdLds& sl) {
   const PopDev* pops;
   const uint64_t* pthr;
@@ -1120,7 +1168,7 @@ __device__ void update_block(const NetDev& nd, uint64_t n, uint32_t blk, UpdLds&
     const uint32_t m = neuron_step<kLif, kAd, P>(nd, pops, pthr, n, i, a, nacc, nrej, capped, mover, nd.npop);
     spk = m > 0;
     entry = i | (m << kMultShift);
-    if (spk && nd.n_rules) nd.last_post[i] = (uint32_t)(n + 1);
+    if (kPl && spk && nd.n_rules) nd.last_post[i] = (uint32_t)(n + 1);
   }
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const uint64_t bal = __ballot(spk);
@@ -1157,7 +1205,7 @@ __device__ void update_block(const NetDev& nd, uint64_t n, uint32_t blk, UpdLds&
     __syncthreads();
     if (sh.npair) {
       pairs += sh.npair;
-      events += dlv_flush(nd, sh, 0u);
+      events += dlv_flush<kPl>(nd, sh, 0u);
     }
   }
   uint64_t sa = 0, sr = 0;
@@ -1234,7 +1282,7 @@ __device__ __forceinline__ uint32_t adex_store(const NetDev& nd, uint32_t i, Ade
 // a lane whose neuron has reached the step end takes the next one, so waves
 // stay full while neurons near a spike need many RK45 substeps and the
 // others one.
-template <bool kLif, int kAd, int P, bool kWin = false>
+template <bool kLif, int kAd, int P, bool kPl, bool kWin>
 __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl) {
   const uint32_t PP = nd.P, tsh = nd.tile_shift, buf = inbuf(n);
   const uint32_t first = t << tsh;
@@ -1424,7 +1472,7 @@ __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl
       if (m) {
         const uint32_t i = first + loc;
         const uint32_t entry = i | (m << kMultShift);
-        if (nd.n_rules) nd.last_post[i] = (uint32_t)(n + 1);
+        if (kPl && nd.n_rules) nd.last_post[i] = (uint32_t)(n + 1);
         const uint64_t mask = nd.src_mask[i];
         const uint32_t gp = nd.grp_ptr[i];
         emit_spike(nd, n, pos_n, sl.emit + before + woff + (uint32_t)__popcll(bal & lanemask_lt()), entry, gp, mask);
@@ -1435,14 +1483,14 @@ __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl
         __syncthreads();
         if (sh.npair > (uint32_t)(kSelChunk - kB)) {
           pairs += sh.npair;
-          events += dlv_flush(nd, sh, inbuf(n + 1));
+          events += dlv_flush<kPl>(nd, sh, inbuf(n + 1));
         }
       }
     }
     __syncthreads();
     if (sh.npair) {
       pairs += sh.npair;
-      events += dlv_flush(nd, sh, inbuf(n + 1));
+      events += dlv_flush<kPl>(nd, sh, inbuf(n + 1));
     }
   }
   uint64_t sa = 0, sr = 0;
@@ -1472,7 +1520,7 @@ __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl
 //     consecutive items from a queue until it is empty, so that a chunk holds
 //     spikes of few instances, whose targets lie in few tiles (longer runs per
 //     tile in the bins), and blocks that start late take less.
-template <class L>
+template <bool kPl, class L>
 __device__ void deliver_block(const NetDev& nd, uint64_t n, uint32_t b, uint32_t G, L& sh) {
   const uint32_t R = nd.R, dmax = nd.dmax;
   dlv_init(nd, sh);
@@ -1519,7 +1567,7 @@ __device__ void deliver_block(const NetDev& nd, uint64_t n, uint32_t b, uint32_t
       }
       __syncthreads();
       pairs += sh.npair;
-      events += dlv_flush(nd, sh, b1);  // ends with a barrier: j0 may be rewritten
+      events += dlv_flush<kPl>(nd, sh, b1);  // ends with a barrier: j0 may be rewritten
     }
   } else {
     const uint64_t mine = (b < items) ? (items - b + G - 1) / G : 0;
@@ -1531,7 +1579,7 @@ __device__ void deliver_block(const NetDev& nd, uint64_t n, uint32_t b, uint32_t
       }
       __syncthreads();
       pairs += sh.npair;
-      events += dlv_flush(nd, sh, b1);
+      events += dlv_flush<kPl>(nd, sh, b1);
     }
   }
   if (threadIdx.x == 0 && (pairs || events)) {
@@ -1548,39 +1596,42 @@ __device__ void deliver_block(const NetDev& nd, uint64_t n, uint32_t b, uint32_t
 // deliver the earlier steps' spikes whose delay (>= 2)
 // expires now.  The update reads the input buffer of step n; deliveries go to
 // the buffers of the steps they arrive at.
-template <bool kLif, int kAd, int P>
+// kPl: the network has plastic synapses.  Networks without any run kernels
+// without that code: with it the microcircuit's step took 2 % and the
+// 30,000-neuron alpha network's 7 % longer (registers of the shared kernel).
+template <bool kLif, int kAd, int P, bool kPl>
 __global__ void __launch_bounds__(kB) k_step(NetDev nd, uint32_t rel) {
   __shared__ StepLds lds;
   const uint64_t n = nd.ctrl->step_base + rel;
   if (blockIdx.x == 0 && threadIdx.x == 0) step_books(nd, n);
   if (blockIdx.x < nd.nblk_upd) {
-    update_block<kLif, kAd, P>(nd, n, blockIdx.x, lds.upd);
+    update_block<kLif, kAd, P, kPl>(nd, n, blockIdx.x, lds.upd);
   } else {
-    deliver_block(nd, n, blockIdx.x - nd.nblk_upd, gridDim.x - nd.nblk_upd, lds.dlv);
+    deliver_block<kPl>(nd, n, blockIdx.x - nd.nblk_upd, gridDim.x - nd.nblk_upd, lds.dlv);
   }
 }
 
 // A tile block's step.  The LIF-only kernels run only where every tile's
 // populations fit the LDS window (the host launches the AdEx-capable kernel
 // for other LIF-only networks), so they read the tables from LDS only.
-template <bool kLif, int kAd, int P>
+template <bool kLif, int kAd, int P, bool kPl>
 __device__ __forceinline__ void tile_step(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl) {
-  tile_block<kLif, kAd, P, kAd == 0>(nd, n, t, sl);
+  tile_block<kLif, kAd, P, kPl, kAd == 0>(nd, n, t, sl);
 }
 
 // One simulation step n, binned delivery: blocks [0, n_tiles) are the tile
 // blocks (input from their bins, update, emission, delay-1 binning), the
 // remaining blocks bin the earlier steps' spikes whose delay (>= 2) expires
 // now.
-template <bool kLif, int kAd, int P>
+template <bool kLif, int kAd, int P, bool kPl>
 __global__ void __launch_bounds__(kB) k_step_binned(NetDev nd, uint32_t rel) {
   __shared__ BinStepLds lds;
   const uint64_t n = nd.ctrl->step_base + rel;
   if (blockIdx.x == 0 && threadIdx.x == 0) step_books(nd, n);
   if (blockIdx.x < nd.n_tiles) {
-    tile_step<kLif, kAd, P>(nd, n, blockIdx.x, lds.tile);
+    tile_step<kLif, kAd, P, kPl>(nd, n, blockIdx.x, lds.tile);
   } else {
-    deliver_block(nd, n, blockIdx.x - nd.n_tiles, gridDim.x - nd.n_tiles, lds.dlv);
+    deliver_block<kPl>(nd, n, blockIdx.x - nd.n_tiles, gridDim.x - nd.n_tiles, lds.dlv);
   }
 }
 
@@ -1593,9 +1644,9 @@ __global__ void __launch_bounds__(kB) k_step_binned_runs(NetDev nd, uint32_t rel
   const uint64_t n = nd.ctrl->step_base + rel;
   if (blockIdx.x == 0 && threadIdx.x == 0) step_books(nd, n);
   if (blockIdx.x < nd.n_tiles) {
-    tile_step<kLif, kAd, P>(nd, n, blockIdx.x, lds.tile);
+    tile_step<kLif, kAd, P, false>(nd, n, blockIdx.x, lds.tile);
   } else {
-    deliver_block(nd, n, blockIdx.x - nd.n_tiles, gridDim.x - nd.n_tiles, lds.dlv);
+    deliver_block<false>(nd, n, blockIdx.x - nd.n_tiles, gridDim.x - nd.n_tiles, lds.dlv);
   }
 }
 
@@ -1607,38 +1658,38 @@ static inline void launch(K kernel, dim3 grid, dim3 blk, hipStream_t s, hipEvent
   else hipLaunchKernelGGL(kernel, grid, blk, 0, s, args...);
 }
 
-template <template <bool, int, int> class Sel, bool kLif, int kAd>
+template <template <bool, int, int, bool> class Sel, bool kLif, int kAd, bool kPl>
 static inline void launch_ports(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop,
                          uint32_t rel) {
   const dim3 blk(kB);
   switch (nd.P) {
-    case 1: launch(Sel<kLif, kAd, 1>::fn(), grid, blk, s, start, stop, nd, rel); break;
-    case 2: launch(Sel<kLif, kAd, 2>::fn(), grid, blk, s, start, stop, nd, rel); break;
-    case 3: launch(Sel<kLif, kAd, 3>::fn(), grid, blk, s, start, stop, nd, rel); break;
-    default: launch(Sel<kLif, kAd, 4>::fn(), grid, blk, s, start, stop, nd, rel); break;
+    case 1: launch(Sel<kLif, kAd, 1, kPl>::fn(), grid, blk, s, start, stop, nd, rel); break;
+    case 2: launch(Sel<kLif, kAd, 2, kPl>::fn(), grid, blk, s, start, stop, nd, rel); break;
+    case 3: launch(Sel<kLif, kAd, 3, kPl>::fn(), grid, blk, s, start, stop, nd, rel); break;
+    default: launch(Sel<kLif, kAd, 4, kPl>::fn(), grid, blk, s, start, stop, nd, rel); break;
   }
 }
 
-template <bool A, int B, int C>
+template <bool A, int B, int C, bool D>
 struct SelDirect {
-  static auto fn() { return k_step<A, B, C>; }
+  static auto fn() { return k_step<A, B, C, D>; }
 };
-template <bool A, int B, int C>
+template <bool A, int B, int C, bool D>
 struct SelBinned {
-  static auto fn() { return k_step_binned<A, B, C>; }
+  static auto fn() { return k_step_binned<A, B, C, D>; }
 };
 
 // which models are present is encoded in nd.pad0: bit 0 LIF, bit 1 AdEx, bit 2
 // AdEx with beta ports
-template <int kAd>
+template <int kAd, bool kPl>
 static void launch_adex(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,
                         bool lif) {
   if (nd.n_tiles) {
-    if (lif) launch_ports<SelBinned, true, kAd>(nd, grid, s, start, stop, rel);
-    else launch_ports<SelBinned, false, kAd>(nd, grid, s, start, stop, rel);
+    if (lif) launch_ports<SelBinned, true, kAd, kPl>(nd, grid, s, start, stop, rel);
+    else launch_ports<SelBinned, false, kAd, kPl>(nd, grid, s, start, stop, rel);
   } else {
-    if (lif) launch_ports<SelDirect, true, kAd>(nd, grid, s, start, stop, rel);
-    else launch_ports<SelDirect, false, kAd>(nd, grid, s, start, stop, rel);
+    if (lif) launch_ports<SelDirect, true, kAd, kPl>(nd, grid, s, start, stop, rel);
+    else launch_ports<SelDirect, false, kAd, kPl>(nd, grid, s, start, stop, rel);
   }
 }
 

@@ -181,3 +181,29 @@ def test_plastic_snapshot_continues(snn):
             b.close()
     finally:
         a.close()
+
+
+@pytest.mark.parametrize("delivery", ["direct", "binned"])
+@pytest.mark.parametrize("n_tgt", [1, 63, 64, 65, 257, 1025])
+def test_arrival_list_places(snn, n_tgt, delivery):
+    """A few generators onto n_tgt neurons through a plastic and a static
+    projection: a step's arrivals fill a wave, a block and a round of the flat
+    scan exactly, fall one short or one over, and mix plastic with static
+    synapses; every weight equals the oracle's."""
+    lif = dict(tau_m=10.0, C_m=250.0, E_L=0.0, V_th=15.0, V_reset=0.0, t_ref=1.0)
+    times = [[1.0, 3.3, 6.0], [1.0, 4.1], [2.5, 6.0, 6.1]]
+    stdp = dict(tau_plus=10.0, tau_minus=12.0, alpha=1.0, mu_plus=1, mu_minus=1, w_max=9.0, **{"lambda": 0.1})
+    pops = [dict(name="G", model="spike_generator", n=3, ports=1, params={}, spike_times=times),
+            dict(name="T", model="lif_delta", n=n_tgt, ports=1, params=lif, V0=np.linspace(0.0, 14.5, n_tgt), I_e=0.0)]
+    projs = [dict(src="G", tgt="T", rule="all_to_all", weight=4.0, delay=("const", 0.5, 0.0), port=0, stdp=stdp),
+             dict(src="G", tgt="T", rule="all_to_all", weight=1.5, delay=("const", 0.5, 0.0), port=0)]
+    spec = dict(name="places", dt=0.1, seed=3, dmax=8, populations=pops, projections=projs, poisson=[])
+    o = O.OracleNet(spec, O.FP32SO)
+    o.simulate(100)
+    g = snn.Net(spec, delivery=delivery)
+    try:
+        g.simulate(100)
+        assert np.array_equal(g.spikes()[1], o.spikes()[1])
+        assert np.array_equal(g.weights(), o.synapses()["wq"])
+    finally:
+        g.close()
