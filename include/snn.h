@@ -176,9 +176,12 @@ typedef struct snn_counters {
                                  graph launches (kernels and the gaps between) */
   uint32_t tile_runs;       /* binned, LIF-only, no plastic synapses: 1 when the
                                groups put on average at least 4 synapses on each
-                               tile they reach and the delivery's count pass reads
-                               their tile runs (recorded at build, 4 bytes per run,
-                               8 per group) instead of every synapse word     */
+                               tile they reach and delivery reads an index of
+                               these runs: the targets pull their input along it
+                               (at most 4 weight classes onto a neuron, no bin
+                               size asked for), or the bins' count pass reads
+                               them (4 bytes per run, 8 per group) instead of
+                               every synapse word                             */
   uint32_t tile_window;     /* binned: 1 when every tile overlaps at most 8
                                populations, so that LIF-only networks run step
                                kernels that read the population tables from a

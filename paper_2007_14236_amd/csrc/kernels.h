@@ -50,6 +50,16 @@ hipError_t launch_runs(bool fill, const uint64_t* grp_off, uint64_t n_groups, co
 // the kernel's own dispatch.
 hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start = nullptr,
                        hipEvent_t stop = nullptr);
+// Pulled delivery (LIF networks with nd.n_pull): one step, the run index and the
+// 16-bit synapses of one instance (sets *too_long for a group of kRunMaxGroup synapses or more),
+// the waiting input into acc[buf], and what a restored snapshot needs: waiting
+// bins into acc[buf], records by slice (tmp: N records).
+void launch_pull_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+hipError_t launch_pull_rows(const NetDev& nd, const PullInst& pi, uint64_t groups, uint32_t* row, uint32_t* too_long,
+                            hipStream_t s);
+hipError_t launch_pull_pay(const NetDev& nd, const PullInst& pi, uint64_t syn, uint16_t* pay, hipStream_t s);
+hipError_t launch_pull_fold(const NetDev& nd, uint32_t buf, hipStream_t s);
+hipError_t launch_pull_restore(const NetDev& nd, uint32_t buf, SpikeRec* tmp, hipStream_t s);
 // The step kernels of networks with AdEx neurons: exponential ports only or
 // with beta ports, without or with plastic synapses (launch_step picks one).
 void launch_adex_exp(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,

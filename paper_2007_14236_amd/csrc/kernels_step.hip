@@ -47,6 +47,10 @@ hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t
   const dim3 blk(kB), grid((nd.n_tiles ? nd.n_tiles : nd.nblk_upd) + nd.sel_grid);
   const bool lif = nd.pad0 & 1u, adex = nd.pad0 & 2u, beta = nd.pad0 & 4u;
   const bool plastic = nd.n_rules != 0;
+  if (nd.n_pull) {
+    launch_pull_step(nd, rel, s, start, stop);
+    return hipGetLastError();
+  }
   if (adex || (nd.n_tiles && !nd.tile_win)) {  // or a tile overlaps more populations than its LDS window holds
     auto f = beta ? (plastic ? launch_adex_beta_plastic : launch_adex_beta)
                   : (plastic ? launch_adex_exp_plastic : launch_adex_exp);

@@ -33,6 +33,7 @@ constexpr uint32_t kGraphSteps = 100;
 constexpr int kNumParams = 16;  // SNN_P_TAU_M .. SNN_P_RK_HMIN
 constexpr uint64_t kChunkRing = 4096;  // >= drain interval + graph length
 constexpr uint64_t kBinnedMinSynapses = 500000000;  // default delivery: binned from this size on
+constexpr uint64_t kPullMinMean = 4; // pulled delivery when the (group, tile) runs average this many synapses
 constexpr uint64_t kRunMinMean = 4;  // tile runs when groups average this many synapses per touched tile
 constexpr uint64_t kQueueMinInstances = 8;          // binned batches with at least this many instances ...
 constexpr uint64_t kQueueMaxTilesPerInstance = 32;  // ... of at most this many tiles each use the delivery queue
@@ -271,6 +272,7 @@ struct snn_net {
   uint32_t* pinned = nullptr;   // staging of a window's ring entries
   size_t pinned_words = 0;
   uint32_t tile_neurons = 0;       // binned delivery (0: direct)
+  uint64_t acc_step = ~0ull;       // pulled delivery: the step whose input a restore left in acc
 
   // host raster
   // host raster: drained entries (gid | mult << 27) with their step, in step
@@ -471,6 +473,14 @@ snn_status drain_advance(snn_net* net);
 void sort_raster(snn_net* net);
 snn_status build_graphs(snn_net* net);
 snn_status collect_samples(snn_net* net, uint64_t from, uint64_t to);
+
+// Pulled delivery: the next step's input as int64 sums in acc, where the
+// readback and the snapshot look for it (it is there already after a restore).
+snn_status pull_fold(snn_net* net) {
+  if (!net->nd.n_pull || net->acc_step == net->cur_step) return SNN_OK;
+  HIPCHK(net, launch_pull_fold(net->nd, (uint32_t)(net->cur_step % kInBuf), net->stream));
+  return SNN_OK;
+}
 
 // ---- snapshot layout: a header, then the dynamic device arrays in order ----
 struct SnapHeader {
@@ -997,6 +1007,7 @@ snn_status snn_snapshot(snn_net* net, void* buf, size_t cap) {
   if (st) return st;
   st = drain(net);  // the raster so far, and no copy in flight
   if (st) return st;
+  if ((st = pull_fold(net))) return st;
   HIPCHK(net, hipStreamSynchronize(net->stream));
   const SnapHeader h = snap_header(net);
   if (cap < h.bytes) return fail(net, SNN_E_INVALID, "snapshot needs %llu bytes", (unsigned long long)h.bytes);
@@ -1005,6 +1016,8 @@ snn_status snn_snapshot(snn_net* net, void* buf, size_t cap) {
   size_t off = sizeof h;
   for (const auto& x : state_arrays(net)) {
     HIPCHK(net, copy_sync(net, out + off, x.first, x.second, hipMemcpyDeviceToHost));
+    if (net->nd.n_pull && x.first == net->nd.acc)  // no input waits there but the next step's
+      memset(out + off + (net->cur_step + 1) % kInBuf * (x.second / kInBuf), 0, x.second / kInBuf);
     off += x.second;
   }
   return leave(net);
@@ -1033,6 +1046,15 @@ snn_status snn_restore(snn_net* net, const void* buf, size_t size) {
   for (const auto& x : state_arrays(net)) {
     HIPCHK(net, copy_sync(net, x.first, in + off, x.second, hipMemcpyHostToDevice));
     off += x.second;
+  }
+  if (net->nd.n_pull) {  // the next step takes its input from acc
+    SpikeRec* tmp = dalloc<SpikeRec>(net, net->nd.N);
+    if (!tmp) return fail(net, SNN_E_NOMEM, "allocation failed");
+    hipError_t e = launch_pull_restore(net->nd, (uint32_t)(h.cur_step % kInBuf), tmp, net->stream);
+    if (e == hipSuccess) e = copy_sync(net, net->nd.pull_acc_step, &h.cur_step, 8, hipMemcpyHostToDevice);
+    dev_free(net, tmp);
+    if (e != hipSuccess) return fail(net, SNN_E_DEVICE, "restore: %s", hipGetErrorString(e));
+    net->acc_step = h.cur_step;
   }
   net->cur_step = net->drained_step = h.cur_step;
   net->dj = snn_net::Drain();
@@ -1259,6 +1281,155 @@ snn_status snn_build(snn_net* net) {
 }  // extern "C"
 
 namespace {
+
+// Pulled delivery (kernels_pull.hip): its tables and run index.  pop_cls: the
+// weight classes onto each population.  Leaves nd.n_pull 0, with nothing
+// allocated, where it does not apply: more than four classes onto a
+// population, counts that could pass 16 bits, runs too short, more tiles or
+// populations of a slice than the kernels hold, or no memory for it.
+snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
+  NetDev& nd = net->nd;
+  hipStream_t s = net->stream;
+  const uint32_t npop = nd.npop, ncls = nd.n_classes;
+  const size_t ni = net->insts.size();
+  // most synapses onto a neuron, times the most spikes a source sends in a step
+  std::vector<uint64_t> most(npop, 0);
+  for (const HostProj& pr : net->projs) {
+    if (!pr.synapses()) continue;
+    uint64_t m = 1;
+    for (const HostPop& p : net->pops)
+      if ((p.model == SNN_SPIKE_GENERATOR || p.model == SNN_PARROT_NEURON) && p.first < pr.src_first + pr.src_n &&
+          p.first + p.n > pr.src_first)
+        m = kMaxMult;
+    const bool bounded = pr.rule == SNN_RULE_FIXED_INDEGREE || pr.rule == SNN_RULE_ALL_TO_ALL || pr.rule == SNN_RULE_ONE_TO_ONE;
+    for (uint32_t k = 0; k < npop; ++k) {
+      const HostPop& p = net->pops[k];
+      if (pr.tgt_first < p.first + p.n && pr.tgt_first + pr.tgt_n > p.first) most[k] += m * (bounded ? pr.K : pr.synapses());
+    }
+  }
+  // a place for each class among the counts of a neuron, no two classes of one population alike
+  std::vector<uint8_t> slot(ncls, 0);
+  std::vector<uint32_t> taken(npop, 0);
+  std::vector<PullPop> pp(npop);
+  uint32_t top = 0;
+  for (uint32_t k = 0; k < npop; ++k) {
+    memset(&pp[k], 0, sizeof(PullPop));
+    if (most[k] > 0xffffu || pop_cls[k].size() > (size_t)kPullSlots) return SNN_OK;
+  }
+  for (uint32_t c = 0; c < ncls; ++c) {
+    uint32_t no = 0;
+    bool used = false;
+    for (uint32_t k = 0; k < npop; ++k)
+      if (std::binary_search(pop_cls[k].begin(), pop_cls[k].end(), c)) { no |= taken[k]; used = true; }
+    if (!used) continue;
+    uint32_t q = 0;
+    while (q < (uint32_t)kPullSlots && (no >> q & 1u)) ++q;
+    if (q == (uint32_t)kPullSlots) return SNN_OK;
+    slot[c] = (uint8_t)q;
+    top = std::max(top, q);
+    for (uint32_t k = 0; k < npop; ++k)
+      if (std::binary_search(pop_cls[k].begin(), pop_cls[k].end(), c)) {
+        taken[k] |= 1u << q;
+        pp[k].wq[q] = net->cls_wq[c];
+        pp[k].port[q] = net->cls_port[c];
+      }
+  }
+  const uint32_t nw = top < 2 ? 1 : 2;
+  std::vector<uint64_t> syn(ni, 0);
+  for (const HostProj& pr : net->projs) syn[pr.inst] += pr.synapses();
+  std::vector<uint32_t> g(ni + 1, 0);
+  for (size_t i = 0; i <= ni; ++i) {  // first group of every instance
+    const uint32_t gid = i < ni ? net->insts[i].first_gid : nd.N;
+    HIPCHK(net, hipMemcpyAsync(&g[i], nd.grp_ptr + gid, 4, hipMemcpyDeviceToHost, s));
+  }
+  HIPCHK(net, hipStreamSynchronize(s));
+  std::vector<PullInst> pi(ni);
+  std::vector<PullSlice> sl;
+  std::vector<PullTile> tl;
+  uint64_t rows = 0, syn0 = 0, pay0 = 0;
+  for (size_t i = 0; i < ni; ++i) {
+    PullInst& p = pi[i];
+    memset(&p, 0, sizeof p);
+    const uint32_t gid0 = net->insts[i].first_gid, gid1 = i + 1 < ni ? net->insts[i + 1].first_gid : nd.N, n = gid1 - gid0;
+    if (syn[i] >= (1ull << 32)) return SNN_OK;
+    p.g0 = g[i]; p.syn0 = syn0; p.pay0 = pay0; p.row0 = rows;
+    p.s0 = (uint32_t)sl.size(); p.t0 = (uint32_t)tl.size();
+    syn0 += syn[i];
+    pay0 += (syn[i] + 1) & ~1ull;
+    const uint32_t per = kPullWords / kPullSlice / nw;  // slices of a tile, at most
+    p.ns = (n + kPullSlice - 1) / kPullSlice;
+    p.nt = (p.ns + per - 1) / per;
+    for (uint32_t t = 0, q = 0; t < p.nt; ++t) {  // slices of equal size, tiles of equal numbers of them
+      PullTile x;
+      memset(&x, 0, sizeof x);
+      x.inst = (uint32_t)i; x.k = t;
+      x.mean_run = (float)((double)syn[i] / ((double)std::max<uint64_t>(1, g[i + 1] - g[i]) * p.nt));
+      for (const uint32_t q1 = (uint32_t)((uint64_t)p.ns * (t + 1) / p.nt); q < q1; ++q) {
+        PullSlice y;
+        y.first = gid0 + (uint32_t)((uint64_t)n * q / p.ns);
+        y.n = gid0 + (uint32_t)((uint64_t)n * (q + 1) / p.ns) - y.first;
+        y.inst = (uint32_t)i; y.tile = (uint32_t)tl.size();
+        if (pop_of(net, y.first + y.n - 1) - pop_of(net, y.first) + 1 > (int)kTilePopLds) return SNN_OK;
+        if (!x.n) x.first = y.first;
+        x.n += y.n;
+        sl.push_back(y);
+      }
+      tl.push_back(x);
+    }
+    rows += (uint64_t)(g[i + 1] - g[i]) * p.nt + 1;
+  }
+  if (tl.size() > kPullMaxTiles || sl.size() > kPullMaxSlices || nd.n_syn < kPullMinMean * rows) return SNN_OK;
+  const size_t words = (size_t)kPullParts * nd.N * nw;
+  uint32_t* d_row = dalloc<uint32_t>(net, rows);
+  uint16_t* d_pay = dalloc<uint16_t>(net, pay0 + 2);
+  PullInst* d_pi = dalloc<PullInst>(net, ni);
+  PullTile* d_tl = dalloc<PullTile>(net, tl.size());
+  PullSlice* d_sl = dalloc<PullSlice>(net, sl.size());
+  PullPop* d_pp = dalloc<PullPop>(net, npop);
+  uint8_t* d_slot = dalloc<uint8_t>(net, ncls);
+  SpkRange* d_spk = dalloc<SpkRange>(net, (size_t)nd.R * sl.size());
+  uint32_t* d_ispk = dalloc<uint32_t>(net, (size_t)nd.R * ni);
+  uint32_t* d_cnt = dalloc<uint32_t>(net, words);
+  uint32_t* d_parts = dalloc<uint32_t>(net, tl.size());
+  uint64_t* d_step = dalloc<uint64_t>(net, 1);
+  uint32_t* d_long = dalloc<uint32_t>(net, 1);
+  void* all[] = {d_row, d_pay, d_pi, d_tl, d_sl, d_pp, d_slot, d_spk, d_ispk, d_cnt, d_parts, d_step};
+  uint32_t no = d_long ? 0 : 1;
+  for (void* p : all) no |= !p;
+  if (!no) {
+    const std::vector<uint32_t> ones(std::max<size_t>(tl.size(), (size_t)kInBuf * nd.n_tiles), 1u);
+    HIPCHK(net, copy_sync(net, d_pi, pi.data(), ni * sizeof(PullInst), hipMemcpyHostToDevice));
+    HIPCHK(net, copy_sync(net, d_tl, tl.data(), tl.size() * sizeof(PullTile), hipMemcpyHostToDevice));
+    HIPCHK(net, copy_sync(net, d_sl, sl.data(), sl.size() * sizeof(PullSlice), hipMemcpyHostToDevice));
+    HIPCHK(net, copy_sync(net, d_pp, pp.data(), npop * sizeof(PullPop), hipMemcpyHostToDevice));
+    HIPCHK(net, copy_sync(net, d_slot, slot.data(), ncls, hipMemcpyHostToDevice));
+    HIPCHK(net, copy_sync(net, d_parts, ones.data(), tl.size() * 4, hipMemcpyHostToDevice));
+    // a build of this network that delivers through bins adds acc where this is set
+    HIPCHK(net, copy_sync(net, nd.ovf_flag, ones.data(), (size_t)kInBuf * nd.n_tiles * 4, hipMemcpyHostToDevice));
+    HIPCHK(net, hipMemsetAsync(d_spk, 0, (size_t)nd.R * sl.size() * sizeof(SpkRange), s));
+    HIPCHK(net, hipMemsetAsync(d_ispk, 0, (size_t)nd.R * ni * 4, s));
+    HIPCHK(net, hipMemsetAsync(d_cnt, 0, (size_t)nd.N * nw * 4, s));
+    HIPCHK(net, hipMemsetAsync(d_step, 0xff, 8, s));
+    HIPCHK(net, hipMemsetAsync(d_long, 0, 4, s));
+    nd.pull_tile = d_tl; nd.pull_slot = d_slot; nd.pull_words = nw;
+    for (size_t i = 0; i < ni; ++i) {
+      if (!pi[i].nt) continue;
+      HIPCHK(net, launch_pull_rows(nd, pi[i], g[i + 1] - g[i], d_row + pi[i].row0, d_long, s));
+      HIPCHK(net, launch_pull_pay(nd, pi[i], syn[i], d_pay, s));
+    }
+    HIPCHK(net, copy_sync(net, &no, d_long, 4, hipMemcpyDeviceToHost));
+  }
+  dev_free(net, d_long);
+  if (no) {
+    for (void* p : all) dev_free(net, p);
+    nd.pull_tile = nullptr;
+    return SNN_OK;
+  }
+  nd.pull_row = d_row; nd.pull_pay = d_pay; nd.pull_inst = d_pi; nd.pull_slice = d_sl; nd.pull_pop = d_pp;
+  nd.slice_spk = d_spk; nd.inst_spk = d_ispk; nd.pull_cnt = d_cnt; nd.pull_parts = d_parts; nd.pull_acc_step = d_step;
+  nd.n_pull = (uint32_t)ni; nd.n_slices = (uint32_t)sl.size(); nd.n_ptiles = (uint32_t)tl.size();
+  return SNN_OK;
+}
 
 snn_status build_impl(snn_net* net) {
   snn_status st = enter(net);
@@ -1949,7 +2120,29 @@ snn_status build_impl(snn_net* net) {
         HIPCHK(net, hipMemcpyAsync(&too_long, d_tl, 4, hipMemcpyDeviceToHost, s));
         HIPCHK(net, hipStreamSynchronize(s));
         dev_free(net, d_rc); dev_free(net, d_tl); dev_free(net, d_rt);
-        if (!too_long && total && nd.n_syn >= kRunMinMean * total) {
+        const bool runs = !too_long && total && nd.n_syn >= kRunMinMean * total;
+        // the targets pull their input (kernels_pull.hip) unless a bin size was asked for
+        if (runs && !net->cfg.bin_capacity) {
+          std::vector<std::vector<uint32_t>> pop_cls(npop);  // ascending
+          for (size_t p = 0; p < net->projs.size(); ++p) {
+            if (!net->projs[p].synapses()) continue;
+            for (uint32_t k = 0; k < npop; ++k) {
+              if (!overlaps(k, net->projs[p].tgt_first, net->projs[p].tgt_n)) continue;
+              const size_t L = net->projs[p].wlev.size();
+              if (!L) pop_cls[k].push_back(cls_of[p * npop + k]);
+              for (size_t l = 0; l < L; ++l) pop_cls[k].push_back(wcls[wcls_off[p] + (k - wpop0[p]) * L + l]);
+            }
+          }
+          for (auto& v : pop_cls) {
+            std::sort(v.begin(), v.end());
+            v.erase(std::unique(v.begin(), v.end()), v.end());
+          }
+          if ((st = build_pull(net, pop_cls))) return st;
+        }
+        if (nd.n_pull) {
+          dev_free(net, d_gr);
+          nd.tile_runs = 1;
+        } else if (runs) {
           uint32_t* d_rd; ALLOC(d_rd, uint32_t, total);
           HIPCHK(net, launch_runs(true, nd.grp_off, G, nd.payload, nd.cls_bits, tsh, nullptr, d_gr, d_rd, nullptr, s));
           nd.grp_run = d_gr; nd.run_desc = d_rd; nd.tile_runs = 1;
@@ -2201,6 +2394,7 @@ snn_status snn_get_input(snn_net* net, uint32_t first, uint32_t n, uint32_t port
   if ((uint64_t)first + n > net->N || port >= net->P) return fail(net, SNN_E_INVALID, "bad range");
   snn_status st = enter(net);
   if (st) return st;
+  if ((st = pull_fold(net))) return st;
   HIPCHK(net, hipStreamSynchronize(net->stream));
   const uint32_t buf = (uint32_t)(net->cur_step % kInBuf);
   const int64_t* base = net->nd.acc + (size_t)buf * net->N * net->P;
@@ -2235,6 +2429,7 @@ snn_status snn_get_input_noalloc(snn_net* net, uint32_t first, uint32_t n, uint3
   snn_status st = enter(net);
   if (st) return st;
   if (n == 0) return leave(net);
+  if ((st = pull_fold(net))) return st;
   const uint32_t buf = (uint32_t)(net->cur_step % kInBuf);
   const int64_t* src = net->nd.acc + (size_t)buf * net->N * net->P + (size_t)first * net->P + port;
   if (!net->nd.n_tiles) {  // direct delivery: the accumulators hold the whole input

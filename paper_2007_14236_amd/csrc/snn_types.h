@@ -155,6 +155,43 @@ struct StdpRule {
 // kernels that read the population tables from LDS only.
 constexpr uint32_t kTilePopLds = 8;
 
+// Pulled delivery (n_pull instances, 0: off).  Every instance is cut into
+// slices of at most kPullSlice neurons (a block of the update) and these into
+// tiles of at most kPullWords 32-bit words of counts (a block's LDS).
+constexpr int kPullSlice = 4096;
+constexpr int kPullWords = 32768;
+constexpr int kPullSlots = 4;              // weight classes onto a neuron, 16-bit counts, two to a word
+constexpr int kPullParts = 24;             // most parts of a tile
+constexpr uint32_t kPullMaxTiles = 512;
+constexpr uint32_t kPullMaxSlices = 4096;
+constexpr uint32_t kPullGrid = 256;        // a block of k_pull on each CU
+// An instance's slices [s0, s0 + ns), tiles [t0, t0 + nt), first group and
+// synapse, and where its 16-bit synapses (an even place) and its run index
+// start: row k of group g is pull_row[row0 + (g - g0) * nt + k], counted from
+// the instance's first synapse.
+struct PullInst {
+  uint32_t s0, ns, t0, nt;
+  uint32_t g0, pad;
+  uint64_t syn0, pay0, row0;
+};
+struct PullTile {
+  uint32_t first, n, inst, k;  // k-th tile of instance inst
+  float mean_run;              // synapses of the instance per (group, tile)
+  uint32_t pad;
+};
+struct PullSlice {
+  uint32_t first, n, inst, tile;
+};
+// Weight and port of a population's counts.
+struct PullPop {
+  int64_t wq[kPullSlots];
+  uint32_t port[kPullSlots];
+};
+// Positions [begin, end) of a slice's spikes among the spikes of their step.
+struct SpkRange {
+  uint32_t begin, end;
+};
+
 struct NetDev {
   uint32_t N, P, npop, dmax;   // dmax = largest delay present
   uint32_t npois, pois_len;    // Poisson threshold tables; entries read at most (the rest are never reached)
@@ -214,6 +251,23 @@ struct NetDev {
   // synapse order (a group is sorted by target)
   const uint64_t* grp_run;
   const uint32_t* run_desc;
+  // pulled delivery: its tables; per step slot the spikes of each slice
+  // (slice_spk[R][n_slices]) and each instance (inst_spk[R][n_pull]); the counts
+  // of the next step's input, pull_cnt[kPullParts][N][pull_words], and the parts
+  // of each tile that hold some; the step whose input lies in acc instead
+  uint32_t n_pull, n_slices, n_ptiles, pull_words;
+  const PullInst* pull_inst;
+  const PullTile* pull_tile;
+  const PullSlice* pull_slice;
+  const PullPop* pull_pop;     // [npop]
+  const uint8_t* pull_slot;    // [n_classes]
+  const uint32_t* pull_row;
+  const uint16_t* pull_pay;
+  SpkRange* slice_spk;
+  uint32_t* inst_spk;
+  uint32_t* pull_cnt;
+  uint32_t* pull_parts;        // [n_ptiles]
+  uint64_t* pull_acc_step;
 };
 
 }  // namespace snn

@@ -154,13 +154,17 @@ __device__ __forceinline__ bool lif_exp_step(const PopDev& pp, const LifK& k, fl
                                              float Ie, const float* x) {
   if (r == 0) {
     float v = __fmul_rn(k.P22, y);
-    for (int p = 0; p < pp.n_ports; ++p) v = __fadd_rn(v, __fmul_rn(k.P21[p], I[p]));
+#pragma unroll
+    for (int p = 0; p < kMaxPorts; ++p)  // constant indices: the arrays stay in registers
+      if (p < pp.n_ports) v = __fadd_rn(v, __fmul_rn(k.P21[p], I[p]));
     v = __fadd_rn(v, __fmul_rn(k.P20, Ie));
     y = v;
   } else {
     r -= 1;
   }
-  for (int p = 0; p < pp.n_ports; ++p) I[p] = __fadd_rn(__fmul_rn(pp.P11[p], I[p]), x[p]);
+#pragma unroll
+  for (int p = 0; p < kMaxPorts; ++p)
+    if (p < pp.n_ports) I[p] = __fadd_rn(__fmul_rn(pp.P11[p], I[p]), x[p]);
   if (r == 0 && y >= k.theta) { y = k.y_reset; r = k.n_ref; return true; }
   return false;
 }
@@ -1057,14 +1061,16 @@ __device__ __forceinline__ void load_tables(const NetDev& nd, PopDev* spops, uin
 }
 
 // The population records p0 .. p0 + np - 1 (np <= kTilePopLds) and their
-// Poisson tables in LDS, the tables renumbered by window index.
+// Poisson tables in LDS, the tables renumbered by window index, by a block of
+// kT threads.
+template <int kT = kB>
 __device__ __forceinline__ void load_tile_window(const NetDev& nd, uint32_t p0, uint32_t np, PopDev* spops,
                                                  uint64_t* sthr) {
   const uint32_t words = np * (uint32_t)(sizeof(PopDev) / 4);
-  for (uint32_t w = threadIdx.x; w < words; w += kB)
+  for (uint32_t w = threadIdx.x; w < words; w += kT)
     reinterpret_cast<uint32_t*>(spops)[w] = reinterpret_cast<const uint32_t*>(nd.pops + p0)[w];
   const uint32_t len = nd.pois_len;
-  for (uint32_t w = threadIdx.x; w < np * len; w += kB) {
+  for (uint32_t w = threadIdx.x; w < np * len; w += kT) {
     const uint32_t k = w / len, j = w - k * len;
     const int32_t q = nd.pops[p0 + k].pois;
     if (q >= 0) sthr[k * kPoisKmax + j] = nd.pois_thr[(size_t)q * kPoisKmax + j];
