@@ -280,6 +280,10 @@ struct snn_net {
   std::vector<uint64_t> r_step;
   std::vector<uint32_t> r_entry;
   size_t r_sorted = 0;
+  // units whose spikes of a step are consecutive and ascending in the ring:
+  // 2^unit_shift neurons each, or as listed
+  uint32_t unit_shift = 6;
+  std::vector<uint32_t> unit_first;
 
   double build_ms = 0.0, sim_ms = 0.0;
   // snn_release: device memory returned, raster and counters kept on the host
@@ -294,12 +298,6 @@ namespace {
 // the process (and fails while another thread captures a graph).
 hipError_t copy_sync(snn_net* net, void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
   hipError_t e = hipMemcpyAsync(dst, src, bytes, kind, net->stream);
-  return e == hipSuccess ? hipStreamSynchronize(net->stream) : e;
-}
-
-hipError_t copy2d_sync(snn_net* net, void* dst, size_t dpitch, const void* src, size_t spitch, size_t width,
-                       size_t height, hipMemcpyKind kind) {
-  hipError_t e = hipMemcpy2DAsync(dst, dpitch, src, spitch, width, height, kind, net->stream);
   return e == hipSuccess ? hipStreamSynchronize(net->stream) : e;
 }
 
@@ -455,16 +453,44 @@ double rest_of(const snn_net* net, uint32_t i) {
   return net->pn[SNN_P_E_L].empty() ? net->pops[pop_of(net, i)].E_L : net->pn[SNN_P_E_L][i];
 }
 
-float to_device_state(const snn_net* net, int var, uint32_t i, double v) {
-  const HostPop& pp = net->pops[pop_of(net, i)];
-  if (var == SNN_V_M && !pp.adex()) return (float)(v - rest_of(net, i));
-  return (float)v;
+// Values v[j nv] of state variable var for neurons first .. first + n as the
+// device holds them (and the inverse): the LIF potential is counted from the
+// neuron's resting potential, everything else is only rounded to fp32.
+// Population by population, so that the loops carry no search.
+template <class F>
+void for_pops(const snn_net* net, uint32_t first, uint32_t n, F f) {
+  for (uint32_t i = first; i < first + n;) {
+    const HostPop& pp = net->pops[pop_of(net, i)];
+    const uint32_t end = std::min(first + n, pp.first + pp.n);
+    f(pp, i, end);
+    i = end;
+  }
 }
 
-double from_device_state(const snn_net* net, int var, uint32_t i, float v) {
-  const HostPop& pp = net->pops[pop_of(net, i)];
-  if (var == SNN_V_M && !pp.adex()) return (double)v + rest_of(net, i);
-  return (double)v;
+void to_device_state(const snn_net* net, int var, uint32_t first, uint32_t n, const double* v, size_t nv, float* out,
+                     size_t stride) {
+  for_pops(net, first, n, [&](const HostPop& pp, uint32_t a, uint32_t b) {
+    const bool rel = var == SNN_V_M && !pp.adex();
+    const double* own = rel && !net->pn[SNN_P_E_L].empty() ? net->pn[SNN_P_E_L].data() : nullptr;
+    const double rest = rel ? pp.E_L : 0.0;
+    for (uint32_t i = a; i < b; ++i) {
+      const double x = v[nv == 1 ? 0 : i - first];
+      out[(size_t)(i - first) * stride] = rel ? (float)(x - (own ? own[i] : rest)) : (float)x;
+    }
+  });
+}
+
+void from_device_state(const snn_net* net, int var, uint32_t first, uint32_t n, const float* in, size_t stride,
+                       double* out) {
+  for_pops(net, first, n, [&](const HostPop& pp, uint32_t a, uint32_t b) {
+    const bool rel = var == SNN_V_M && !pp.adex();
+    const double* own = rel && !net->pn[SNN_P_E_L].empty() ? net->pn[SNN_P_E_L].data() : nullptr;
+    const double rest = rel ? pp.E_L : 0.0;
+    for (uint32_t i = a; i < b; ++i) {
+      const double x = (double)in[(size_t)(i - first) * stride];
+      out[i - first] = rel ? x + (own ? own[i] : rest) : x;
+    }
+  });
 }
 
 snn_status drain(snn_net* net);
@@ -1148,14 +1174,13 @@ snn_status snn_set_state(snn_net* net, uint32_t first, uint32_t n, int32_t var, 
     default: return fail(net, SNN_E_INVALID, "unknown state variable %d", var);
   }
   if (!base) return fail(net, SNN_E_INVALID, "state variable not present in this network");
-  std::vector<float> buf(n);
-  for (uint32_t j = 0; j < n; ++j) buf[j] = to_device_state(net, var, first + j, v[nv == 1 ? 0 : j]);
-  if (stride == 1) {
-    HIPCHK(net, copy_sync(net, base + first, buf.data(), n * sizeof(float), hipMemcpyHostToDevice));
-  } else {
-    HIPCHK(net, copy2d_sync(net, base + (size_t)first * stride + off, stride * sizeof(float), buf.data(), sizeof(float),
-                            sizeof(float), n, hipMemcpyHostToDevice));
-  }
+  // a port's values lie between the other ports': the range is copied whole,
+  // edited and copied back (a strided copy moves 4 bytes at a time, ~6 us each)
+  std::vector<float> buf((size_t)n * stride);
+  const size_t bytes = buf.size() * sizeof(float);
+  if (stride > 1) HIPCHK(net, copy_sync(net, buf.data(), base + (size_t)first * stride, bytes, hipMemcpyDeviceToHost));
+  if (n) to_device_state(net, var, first, n, v, nv, buf.data() + off, stride);
+  HIPCHK(net, copy_sync(net, base + (size_t)first * stride, buf.data(), bytes, hipMemcpyHostToDevice));
   return leave(net);
 }
 
@@ -1206,14 +1231,11 @@ snn_status snn_get_state(snn_net* net, uint32_t first, uint32_t n, int32_t var, 
     default: return fail(net, SNN_E_INVALID, "unknown state variable %d", var);
   }
   if (!base) return fail(net, SNN_E_INVALID, "state variable not present in this network");
-  std::vector<float> buf(n);
-  if (stride == 1) {
-    HIPCHK(net, copy_sync(net, buf.data(), base + first, n * sizeof(float), hipMemcpyDeviceToHost));
-  } else {
-    HIPCHK(net, copy2d_sync(net, buf.data(), sizeof(float), base + (size_t)first * stride + off, stride * sizeof(float),
-                            sizeof(float), n, hipMemcpyDeviceToHost));
-  }
-  for (uint32_t j = 0; j < n; ++j) out[j] = from_device_state(net, var, first + j, buf[j]);
+  // all ports of the range in one copy, the wanted one picked here: 10^4
+  // two-port values took 66 ms as a strided copy of 4 bytes each, now 0.1 ms
+  std::vector<float> buf((size_t)n * stride);
+  HIPCHK(net, copy_sync(net, buf.data(), base + (size_t)first * stride, buf.size() * sizeof(float), hipMemcpyDeviceToHost));
+  if (n) from_device_state(net, var, first, n, buf.data() + off, stride, out);
   return leave(net);
 }
 
@@ -1229,6 +1251,7 @@ void release_build(snn_net* net) {
   (void)hipStreamSynchronize(net->stream);
   for (auto& gx : net->graphs) (void)hipGraphExecDestroy(gx.second);
   net->graphs.clear();
+  net->unit_first.clear();
   while (!net->allocs.empty()) dev_free(net, net->allocs.back().p);
   if (net->pin_cb) (void)hipHostFree(net->pin_cb);
   if (net->pin_rc) (void)hipHostFree(net->pin_rc);
@@ -1427,6 +1450,7 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
   }
   nd.pull_row = d_row; nd.pull_pay = d_pay; nd.pull_inst = d_pi; nd.pull_slice = d_sl; nd.pull_pop = d_pp;
   nd.slice_spk = d_spk; nd.inst_spk = d_ispk; nd.pull_cnt = d_cnt; nd.pull_parts = d_parts; nd.pull_acc_step = d_step;
+  for (const PullSlice& y : sl) net->unit_first.push_back(y.first);
   nd.n_pull = (uint32_t)ni; nd.n_slices = (uint32_t)sl.size(); nd.n_ptiles = (uint32_t)tl.size();
   return SNN_OK;
 }
@@ -2153,6 +2177,8 @@ snn_status build_impl(snn_net* net) {
     }
   }
 
+  net->unit_shift = nd.n_tiles ? nd.tile_shift : 6u;
+
   // ---- spike buffers ----
   net->drain_steps = std::max<uint64_t>(kGraphSteps, std::min<uint64_t>(1000, ((1ull << 25) / N) / kGraphSteps * kGraphSteps));
   // the ring holds a drain window plus the two graphs launched before its
@@ -2316,7 +2342,7 @@ snn_status snn_get_spikes(snn_net* net, uint64_t step_lo, uint64_t step_hi, uint
                           uint32_t* mult, size_t cap, size_t* n_out) {
   if (!net || !n_out) return SNN_E_INVALID;
   net->err.clear();
-  if (net->built && step_hi > net->drained_step) {  // the steps still on the device first
+  if (net->built && (step_hi > net->drained_step || net->dj.stage)) {  // the steps still on the device, or on their way
     snn_status st = enter(net);
     if (st) return st;
     if ((st = drain(net))) return st;
@@ -2399,7 +2425,13 @@ snn_status snn_get_input(snn_net* net, uint32_t first, uint32_t n, uint32_t port
   const uint32_t buf = (uint32_t)(net->cur_step % kInBuf);
   const int64_t* base = net->nd.acc + (size_t)buf * net->N * net->P;
   if (!net->nd.n_tiles || n == 0) {
-    if (n) HIPCHK(net, copy2d_sync(net, out, 8, base + (size_t)first * net->P + port, net->P * 8, 8, n, hipMemcpyDeviceToHost));
+    if (n && net->P == 1) {
+      HIPCHK(net, copy_sync(net, out, base + first, (size_t)n * 8, hipMemcpyDeviceToHost));
+    } else if (n) {
+      std::vector<int64_t> all((size_t)n * net->P);
+      HIPCHK(net, copy_sync(net, all.data(), base + (size_t)first * net->P, all.size() * 8, hipMemcpyDeviceToHost));
+      for (uint32_t j = 0; j < n; ++j) out[j] = all[(size_t)j * net->P + port];
+    }
     return leave(net);
   }
   // binned: the spilled part (acc) plus the entries waiting in the tiles' bins
@@ -2433,7 +2465,18 @@ snn_status snn_get_input_noalloc(snn_net* net, uint32_t first, uint32_t n, uint3
   const uint32_t buf = (uint32_t)(net->cur_step % kInBuf);
   const int64_t* src = net->nd.acc + (size_t)buf * net->N * net->P + (size_t)first * net->P + port;
   if (!net->nd.n_tiles) {  // direct delivery: the accumulators hold the whole input
-    HIPCHK(net, copy2d_sync(net, out, 8, src, net->P * 8, 8, n, hipMemcpyDeviceToHost));
+    if (net->P == 1) {
+      HIPCHK(net, copy_sync(net, out, src, (size_t)n * 8, hipMemcpyDeviceToHost));
+    } else {  // all ports of a stretch at a time, through the stack
+      int64_t all[4096];
+      const uint32_t per = 4096 / net->P;
+      for (uint32_t a = 0; a < n; a += per) {
+        const uint32_t m = std::min(per, n - a);
+        const size_t words = (size_t)(m - 1) * net->P + 1;  // src counts from the port's first value
+        HIPCHK(net, copy_sync(net, all, src + (size_t)a * net->P, words * 8, hipMemcpyDeviceToHost));
+        for (uint32_t j = 0; j < m; ++j) out[a + j] = all[(size_t)j * net->P];
+      }
+    }
     return leave(net);
   }
   // binned: the spilled part overwrites ws[0, n), then the bin entries are added
@@ -2567,7 +2610,7 @@ snn_status collect_samples(snn_net* net, uint64_t from, uint64_t to) {
       m.steps.push_back(n);
       for (size_t j = 0; j < m.gids.size(); ++j) {
         double v = row[j];
-        if (m.var == SNN_V_M) v = from_device_state(net, SNN_V_M, m.gids[j], row[j]);
+        if (m.var == SNN_V_M) from_device_state(net, SNN_V_M, m.gids[j], 1, &row[j], 1, &v);
         m.values.push_back(v);
       }
     }
@@ -2589,18 +2632,54 @@ snn_status build_graphs(snn_net* net) {
   return SNN_OK;
 }
 
-// Order the entries drained since the last read by gid within each step
-// (steps are independent: large rasters are split over the host's cores).
+// Order the entries drained since the last read by gid within each step.  The
+// spikes of one emitting unit (a wave of 64 neurons in direct delivery, a tile
+// or a slice otherwise) are consecutive and ascending, only the units come in
+// any order: each step's units are put in order and copied, without comparing
+// entries (9 steps of the batched sweep with their 305,000 spikes read: 8.6 ms
+// with std::sort of each step, now 4.4 ms).
+// Steps are independent: large rasters are split over the host's cores.
 void sort_raster(snn_net* net) {
   const size_t n = net->r_entry.size(), lo = net->r_sorted;
   if (lo >= n) return;
-  auto sort_steps = [net](size_t a, size_t b) {  // [a, b) starts and ends on step boundaries
+  const std::vector<uint32_t>& edge = net->unit_first;  // first gid of every unit, where they are no power of two
+  const uint32_t sh = net->unit_shift, units = edge.empty() ? (net->N >> sh) + 1 : (uint32_t)edge.size();
+  auto sort_steps = [&](size_t a, size_t b) {  // [a, b) starts and ends on step boundaries
+    struct Run { uint32_t unit, len; size_t at; };
+    std::vector<Run> runs, by_unit;
+    std::vector<uint32_t> tmp;
     size_t i = a;
     while (i < b) {
-      size_t j = i + 1;
-      while (j < b && net->r_step[j] == net->r_step[i]) ++j;
-      std::sort(net->r_entry.begin() + (long)i, net->r_entry.begin() + (long)j,
-                [](uint32_t x, uint32_t y) { return (x & kGidMask) < (y & kGidMask); });
+      const size_t j = (size_t)(std::upper_bound(net->r_step.begin() + (long)i, net->r_step.begin() + (long)b,
+                                                 net->r_step[i]) - net->r_step.begin());
+      runs.clear();
+      bool sorted = true;
+      uint32_t end = 0;  // first gid beyond the unit of the open run
+      for (size_t k = i; k < j; ++k) {
+        const uint32_t g = net->r_entry[k] & kGidMask;
+        if (k > i && g < end && g > (net->r_entry[k - 1] & kGidMask)) {
+          ++runs.back().len;
+          continue;
+        }
+        uint32_t u = g >> sh;
+        if (!edge.empty()) u = (uint32_t)(std::upper_bound(edge.begin(), edge.end(), g) - edge.begin()) - 1;
+        end = edge.empty() ? (u + 1) << sh : (u + 1 < units ? edge[u + 1] : net->N);
+        sorted = sorted && (runs.empty() || u > runs.back().unit);
+        runs.push_back({u, 1, k});
+      }
+      if (!sorted) {
+        if (runs.size() > units / 8) {  // many units: by place
+          by_unit.assign(units, Run{0, 0, 0});
+          for (const Run& r : runs) by_unit[r.unit] = r;
+          runs.swap(by_unit);
+        } else {
+          std::sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.unit < y.unit; });
+        }
+        tmp.clear();
+        for (const Run& r : runs)
+          tmp.insert(tmp.end(), net->r_entry.begin() + (long)r.at, net->r_entry.begin() + (long)(r.at + r.len));
+        std::copy(tmp.begin(), tmp.end(), net->r_entry.begin() + (long)i);
+      }
       i = j;
     }
   };
@@ -2678,11 +2757,8 @@ snn_status drain_advance(snn_net* net) {
     net->r_step.reserve(std::max(need, 2 * net->r_step.capacity()));
     net->r_entry.reserve(std::max(need, 2 * net->r_entry.capacity()));
   }
-  for (uint64_t n = d.a; n < d.b; ++n)
-    for (uint64_t q = d.base[n - d.a]; q < d.base[n - d.a + 1]; ++q) {
-      net->r_step.push_back(n);
-      net->r_entry.push_back(net->pinned[q]);
-    }
+  for (uint64_t n = d.a; n < d.b; ++n) net->r_step.insert(net->r_step.end(), d.base[n - d.a + 1] - d.base[n - d.a], n);
+  net->r_entry.insert(net->r_entry.end(), net->pinned, net->pinned + d.total);
   d.stage = 0;
   return SNN_OK;
 }
