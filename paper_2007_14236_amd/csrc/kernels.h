@@ -60,6 +60,15 @@ hipError_t launch_pull_rows(const NetDev& nd, const PullInst& pi, uint64_t group
 hipError_t launch_pull_pay(const NetDev& nd, const PullInst& pi, uint64_t syn, uint16_t* pay, hipStream_t s);
 hipError_t launch_pull_fold(const NetDev& nd, uint32_t buf, hipStream_t s);
 hipError_t launch_pull_restore(const NetDev& nd, uint32_t buf, SpikeRec* tmp, hipStream_t s);
+// Small LIF networks (kernels_small.hip): steps in one launch (advances the
+// step counter itself), what a readback needs, what a restored snapshot needs
+// (ring cleared by the caller), the rows of the sources, the LDS of a block.
+hipError_t launch_small_steps(const NetDev& nd, uint32_t steps, hipStream_t s, hipEvent_t start = nullptr,
+                              hipEvent_t stop = nullptr);
+hipError_t launch_small_fold(const NetDev& nd, hipStream_t s);
+hipError_t launch_small_restore(const NetDev& nd, hipStream_t s);
+hipError_t launch_small_rows(const NetDev& nd, uint32_t* row, uint32_t* pay, hipStream_t s);
+size_t small_lds_bytes(const NetDev& nd);
 // The step kernels of networks with AdEx neurons: exponential ports only or
 // with beta ports, without or with plastic synapses (launch_step picks one).
 void launch_adex_exp(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,

@@ -33,6 +33,8 @@ constexpr uint32_t kGraphSteps = 100;
 constexpr int kNumParams = 16;  // SNN_P_TAU_M .. SNN_P_RK_HMIN
 constexpr uint64_t kChunkRing = 4096;  // >= drain interval + graph length
 constexpr uint64_t kBinnedMinSynapses = 500000000;  // default delivery: binned from this size on
+constexpr uint64_t kSmallSyn = 1u << 19;           // small networks: synapses, at most
+constexpr uint32_t kSmallPops = 16;                // ... populations
 constexpr uint64_t kPullMinMean = 4; // pulled delivery when the (group, tile) runs average this many synapses
 constexpr uint64_t kRunMinMean = 4;  // tile runs when groups average this many synapses per touched tile
 constexpr uint64_t kQueueMinInstances = 8;          // binned batches with at least this many instances ...
@@ -272,6 +274,7 @@ struct snn_net {
   uint32_t* pinned = nullptr;   // staging of a window's ring entries
   size_t pinned_words = 0;
   uint32_t tile_neurons = 0;       // binned delivery (0: direct)
+  size_t small_ring_bytes = 0;
   uint64_t acc_step = ~0ull;       // pulled delivery: the step whose input a restore left in acc
 
   // host raster
@@ -500,9 +503,11 @@ void sort_raster(snn_net* net);
 snn_status build_graphs(snn_net* net);
 snn_status collect_samples(snn_net* net, uint64_t from, uint64_t to);
 
-// Pulled delivery: the next step's input as int64 sums in acc, where the
-// readback and the snapshot look for it (it is there already after a restore).
+// Pulled delivery and small networks: the next step's input as int64 sums in
+// acc, where the readback and the snapshot look for it (with pulled delivery
+// it is there already after a restore); small networks' delivery counters.
 snn_status pull_fold(snn_net* net) {
+  if (net->nd.small_row) HIPCHK(net, launch_small_fold(net->nd, net->stream));
   if (!net->nd.n_pull || net->acc_step == net->cur_step) return SNN_OK;
   HIPCHK(net, launch_pull_fold(net->nd, (uint32_t)(net->cur_step % kInBuf), net->stream));
   return SNN_OK;
@@ -1073,6 +1078,11 @@ snn_status snn_restore(snn_net* net, const void* buf, size_t size) {
     HIPCHK(net, copy_sync(net, x.first, in + off, x.second, hipMemcpyHostToDevice));
     off += x.second;
   }
+  if (net->nd.small_row) {  // the ring from the spikes in flight
+    HIPCHK(net, hipMemsetAsync(net->nd.small_ring, 0, net->small_ring_bytes, net->stream));
+    HIPCHK(net, launch_small_restore(net->nd, net->stream));
+    HIPCHK(net, hipStreamSynchronize(net->stream));
+  }
   if (net->nd.n_pull) {  // the next step takes its input from acc
     SpikeRec* tmp = dalloc<SpikeRec>(net, net->nd.N);
     if (!tmp) return fail(net, SNN_E_NOMEM, "allocation failed");
@@ -1305,16 +1315,15 @@ snn_status snn_build(snn_net* net) {
 
 namespace {
 
-// Pulled delivery (kernels_pull.hip): its tables and run index.  pop_cls: the
-// weight classes onto each population.  Leaves nd.n_pull 0, with nothing
-// allocated, where it does not apply: more than four classes onto a
-// population, counts that could pass 16 bits, runs too short, more tiles or
-// populations of a slice than the kernels hold, or no memory for it.
-snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
-  NetDev& nd = net->nd;
-  hipStream_t s = net->stream;
-  const uint32_t npop = nd.npop, ncls = nd.n_classes;
-  const size_t ni = net->insts.size();
+// 16-bit counts of the weight classes onto a neuron in place of its int64 input
+// (pulled delivery, small networks).  pop_cls: the classes onto each
+// population, ascending.  Gives each class its place among a neuron's counts
+// and each population its places' weights, and returns the 32-bit words of
+// counts a neuron needs; 0 where it does not work: more than four classes onto
+// a population, or counts that could pass 16 bits in a step.
+uint32_t class_slots(const snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls, std::vector<uint8_t>& slot,
+                     std::vector<PullPop>& pp) {
+  const uint32_t npop = (uint32_t)net->pops.size(), ncls = (uint32_t)net->cls_wq.size();
   // most synapses onto a neuron, times the most spikes a source sends in a step
   std::vector<uint64_t> most(npop, 0);
   for (const HostProj& pr : net->projs) {
@@ -1331,13 +1340,13 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
     }
   }
   // a place for each class among the counts of a neuron, no two classes of one population alike
-  std::vector<uint8_t> slot(ncls, 0);
+  slot.assign(ncls, 0);
   std::vector<uint32_t> taken(npop, 0);
-  std::vector<PullPop> pp(npop);
+  pp.resize(npop);
   uint32_t top = 0;
   for (uint32_t k = 0; k < npop; ++k) {
     memset(&pp[k], 0, sizeof(PullPop));
-    if (most[k] > 0xffffu || pop_cls[k].size() > (size_t)kPullSlots) return SNN_OK;
+    if (most[k] > 0xffffu || pop_cls[k].size() > (size_t)kPullSlots) return 0;
   }
   for (uint32_t c = 0; c < ncls; ++c) {
     uint32_t no = 0;
@@ -1347,7 +1356,7 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
     if (!used) continue;
     uint32_t q = 0;
     while (q < (uint32_t)kPullSlots && (no >> q & 1u)) ++q;
-    if (q == (uint32_t)kPullSlots) return SNN_OK;
+    if (q == (uint32_t)kPullSlots) return 0;
     slot[c] = (uint8_t)q;
     top = std::max(top, q);
     for (uint32_t k = 0; k < npop; ++k)
@@ -1357,7 +1366,63 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
         pp[k].port[q] = net->cls_port[c];
       }
   }
-  const uint32_t nw = top < 2 ? 1 : 2;
+  return top < 2 ? 1 : 2;
+}
+
+// A small LIF network (kernels_small.hip): one block runs all steps of a
+// launch.  The line: the ring of inputs fits one block's LDS, and the synapses
+// are few enough that a CU delivers a step's events no later than a launch per
+// step does at any rate (1,000 neurons in LDS: 876 events a step 2.2 us,
+// 16,800 events 6.8 us; by a launch per step 8.1 and 9.0 us; at a rate of a
+// spike per neuron and 2 ms, 2^19 synapses are 26,000 events a step).
+snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
+  NetDev& nd = net->nd;
+  hipStream_t s = net->stream;
+  if (nd.N > kSmallN || nd.P > 2 || nd.npop > kSmallPops || nd.n_syn > kSmallSyn || net->nch) return SNN_OK;
+  std::vector<uint8_t> slot;
+  std::vector<PullPop> pp;
+  NetDev x = nd;
+  x.pull_words = class_slots(net, pop_cls, slot, pp);
+  if (!x.pull_words || small_lds_bytes(x) > kSmallLds) return SNN_OK;
+  const size_t ring = (size_t)nd.R * nd.N * x.pull_words;
+  const size_t old = net->allocs.size();
+  uint32_t* d_row = dalloc<uint32_t>(net, (size_t)nd.N + 1);
+  uint32_t* d_pay = dalloc<uint32_t>(net, std::max<uint64_t>(1, nd.n_syn));
+  uint32_t* d_ring = dalloc<uint32_t>(net, ring);
+  uint8_t* d_pois = dalloc<uint8_t>(net, (size_t)kGraphSteps * nd.N);
+  uint64_t* d_sent = dalloc<uint64_t>(net, 2);
+  PullPop* d_pp = dalloc<PullPop>(net, nd.npop);
+  uint8_t* d_slot = dalloc<uint8_t>(net, std::max<size_t>(1, slot.size()));
+  if (!d_row || !d_pay || !d_ring || !d_pois || !d_sent || !d_pp || !d_slot) {
+    while (net->allocs.size() > old) dev_free(net, net->allocs.back().p);
+    return SNN_OK;
+  }
+  HIPCHK(net, copy_sync(net, d_pp, pp.data(), pp.size() * sizeof(PullPop), hipMemcpyHostToDevice));
+  HIPCHK(net, copy_sync(net, d_slot, slot.data(), slot.size(), hipMemcpyHostToDevice));
+  HIPCHK(net, hipMemsetAsync(d_ring, 0, ring * 4, s));
+  HIPCHK(net, hipMemsetAsync(d_sent, 0, 16, s));
+  x.pull_pop = d_pp; x.pull_slot = d_slot;
+  x.small_row = d_row; x.small_pay = d_pay; x.small_ring = d_ring;
+  x.small_pois = d_pois; x.small_sent = d_sent;
+  HIPCHK(net, launch_small_rows(x, d_row, d_pay, s));
+  net->small_ring_bytes = ring * 4;
+  nd = x;
+  return SNN_OK;
+}
+
+// Pulled delivery (kernels_pull.hip): its tables and run index.  Leaves
+// nd.n_pull 0, with nothing allocated, where it does not apply: no 16-bit
+// counts (class_slots), runs too short, more tiles or populations of a slice
+// than the kernels hold, or no memory for it.
+snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
+  NetDev& nd = net->nd;
+  hipStream_t s = net->stream;
+  const uint32_t npop = nd.npop, ncls = nd.n_classes;
+  const size_t ni = net->insts.size();
+  std::vector<uint8_t> slot;
+  std::vector<PullPop> pp;
+  const uint32_t nw = class_slots(net, pop_cls, slot, pp);
+  if (!nw) return SNN_OK;
   std::vector<uint64_t> syn(ni, 0);
   for (const HostProj& pr : net->projs) syn[pr.inst] += pr.synapses();
   std::vector<uint32_t> g(ni + 1, 0);
@@ -2022,6 +2087,22 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, hipMemsetAsync(d_acc, 0, (size_t)kInBuf * N * P * 8, s));
   nd.acc = d_acc;
 
+  // weight classes onto each population, ascending
+  std::vector<std::vector<uint32_t>> pop_cls(npop);
+  for (size_t p = 0; p < net->projs.size(); ++p) {
+    if (!net->projs[p].synapses()) continue;
+    for (uint32_t k = 0; k < npop; ++k) {
+      if (!overlaps(k, net->projs[p].tgt_first, net->projs[p].tgt_n)) continue;
+      const size_t L = net->projs[p].wlev.size();
+      if (!L) pop_cls[k].push_back(cls_of[p * npop + k]);
+      for (size_t l = 0; l < L; ++l) pop_cls[k].push_back(wcls[wcls_off[p] + (k - wpop0[p]) * L + l]);
+    }
+  }
+  for (auto& v : pop_cls) {
+    std::sort(v.begin(), v.end());
+    v.erase(std::unique(v.begin(), v.end()), v.end());
+  }
+
   // ---- delivery mode: direct atomics or bins per target tile ----
   {
     uint32_t P2 = 1;
@@ -2147,20 +2228,6 @@ snn_status build_impl(snn_net* net) {
         const bool runs = !too_long && total && nd.n_syn >= kRunMinMean * total;
         // the targets pull their input (kernels_pull.hip) unless a bin size was asked for
         if (runs && !net->cfg.bin_capacity) {
-          std::vector<std::vector<uint32_t>> pop_cls(npop);  // ascending
-          for (size_t p = 0; p < net->projs.size(); ++p) {
-            if (!net->projs[p].synapses()) continue;
-            for (uint32_t k = 0; k < npop; ++k) {
-              if (!overlaps(k, net->projs[p].tgt_first, net->projs[p].tgt_n)) continue;
-              const size_t L = net->projs[p].wlev.size();
-              if (!L) pop_cls[k].push_back(cls_of[p * npop + k]);
-              for (size_t l = 0; l < L; ++l) pop_cls[k].push_back(wcls[wcls_off[p] + (k - wpop0[p]) * L + l]);
-            }
-          }
-          for (auto& v : pop_cls) {
-            std::sort(v.begin(), v.end());
-            v.erase(std::unique(v.begin(), v.end()), v.end());
-          }
           if ((st = build_pull(net, pop_cls))) return st;
         }
         if (nd.n_pull) {
@@ -2178,6 +2245,9 @@ snn_status build_impl(snn_net* net) {
   }
 
   net->unit_shift = nd.n_tiles ? nd.tile_shift : 6u;
+  if (!nd.n_tiles && !net->has_adex && !nd.n_rules && !(net->cfg.flags & SNN_F_DELIVERY_DIRECT) &&
+      (st = build_small(net, pop_cls)))
+    return st;
 
   // ---- spike buffers ----
   net->drain_steps = std::max<uint64_t>(kGraphSteps, std::min<uint64_t>(1000, ((1ull << 25) / N) / kGraphSteps * kGraphSteps));
@@ -2263,11 +2333,16 @@ snn_status snn_simulate_steps(snn_net* net, uint64_t steps) {
   uint64_t left = steps;
   while (left > 0) {
     const uint64_t from = net->cur_step;
-    // the longest captured loop that fits: kGraphSteps, then the binary digits of the rest
-    size_t gi = 0;
-    while (net->graphs[gi].first > left) ++gi;
-    const uint32_t len = net->graphs[gi].first;
-    HIPCHK(net, hipGraphLaunch(net->graphs[gi].second, net->stream));
+    uint32_t len = (uint32_t)std::min<uint64_t>(left, kGraphSteps);
+    if (net->nd.small_row) {
+      HIPCHK(net, launch_small_steps(net->nd, len, net->stream));
+    } else {
+      // the longest captured loop that fits: kGraphSteps, then the binary digits of the rest
+      size_t gi = 0;
+      while (net->graphs[gi].first > left) ++gi;
+      len = net->graphs[gi].first;
+      HIPCHK(net, hipGraphLaunch(net->graphs[gi].second, net->stream));
+    }
     net->cur_step += len;
     left -= len;
     if (net->nch) {  // the replay's samples, before the next one overwrites the device window
@@ -2311,10 +2386,14 @@ snn_status snn_profile_steps(snn_net* net, uint64_t steps, double* kernel_ms) {
   for (auto& e : ev) HIPCHK(net, hipEventCreate(&e));
   const auto t0 = std::chrono::steady_clock::now();
   for (uint64_t k = 0; k < steps; ++k) {
-    HIPCHK(net, launch_step(net->nd, 0, net->stream, ev[0], ev[1]));
-    HIPCHK(net, launch_stdp(net->nd, 0, net->stream));
-    HIPCHK(net, launch_sample(net->d_addr, net->nch, net->d_mbuf, kGraphSteps, net->nd.ctrl, 0, net->stream));
-    HIPCHK(net, launch_advance(net->nd.ctrl, 1, net->stream));
+    if (net->nd.small_row) {
+      HIPCHK(net, launch_small_steps(net->nd, 1, net->stream, ev[0], ev[1]));
+    } else {
+      HIPCHK(net, launch_step(net->nd, 0, net->stream, ev[0], ev[1]));
+      HIPCHK(net, launch_stdp(net->nd, 0, net->stream));
+      HIPCHK(net, launch_sample(net->d_addr, net->nch, net->d_mbuf, kGraphSteps, net->nd.ctrl, 0, net->stream));
+      HIPCHK(net, launch_advance(net->nd.ctrl, 1, net->stream));
+    }
     HIPCHK(net, hipEventSynchronize(ev[1]));
     float ms = 0.f;
     HIPCHK(net, hipEventElapsedTime(&ms, ev[0], ev[1]));
@@ -2378,6 +2457,7 @@ snn_status snn_get_counters(snn_net* net, snn_counters* out) {
   if (!net->built) return SNN_OK;
   snn_status st = enter(net);
   if (st) return st;
+  if (net->nd.small_row && (st = pull_fold(net))) return st;
   HIPCHK(net, hipStreamSynchronize(net->stream));
   Ctrl c;
   HIPCHK(net, copy_sync(net, &c, net->nd.ctrl, sizeof c, hipMemcpyDeviceToHost));
@@ -2619,6 +2699,7 @@ snn_status collect_samples(snn_net* net, uint64_t from, uint64_t to) {
 }
 
 snn_status build_graphs(snn_net* net) {
+  if (net->nd.small_row) return SNN_OK;  // one launch runs many steps
   uint32_t lens[16], n = 0;
   lens[n++] = kGraphSteps;
   for (uint32_t len = 1u << 6; len >= 1; len >>= 1)

@@ -165,6 +165,9 @@ constexpr int kPullParts = 24;             // most parts of a tile
 constexpr uint32_t kPullMaxTiles = 512;
 constexpr uint32_t kPullMaxSlices = 4096;
 constexpr uint32_t kPullGrid = 256;        // a block of k_pull on each CU
+// Small networks (small_row set): all steps of a launch in one block.
+constexpr uint32_t kSmallN = 2048;         // neurons, at most: two a thread
+constexpr size_t kSmallLds = 160 * 1024;   // LDS of a block
 // An instance's slices [s0, s0 + ns), tiles [t0, t0 + nt), first group and
 // synapse, and where its 16-bit synapses (an even place) and its run index
 // start: row k of group g is pull_row[row0 + (g - g0) * nt + k], counted from
@@ -268,6 +271,14 @@ struct NetDev {
   uint32_t* pull_cnt;
   uint32_t* pull_parts;        // [n_ptiles]
   uint64_t* pull_acc_step;
+  // small networks: the rows of a source's synapses (target | delay << 13 |
+  // count << 19, in CSR order), the ring of inputs by arrival step between
+  // launches (counts [R][N][pull_words]), the Poisson counts of a launch [steps][N], pairs and events of all spikes sent
+  const uint32_t* small_row;   // [N + 1]
+  const uint32_t* small_pay;
+  uint32_t* small_ring;
+  uint8_t* small_pois;
+  uint64_t* small_sent;        // [2]
 };
 
 }  // namespace snn

@@ -1,0 +1,153 @@
+"""GPU parity of small networks, whose steps run in one block: rasters,
+potentials, pending inputs and counters bit-exact against the oracle and against
+the same network stepped by a launch per step.  Sizes where it can go wrong:
+one neuron, a wave and a block full, one short and one over, two neurons a
+thread; one and two words of counts a neuron; one delay and 63; rows of one synapse, of 64 and of thousands; more spikes in a step
+than a wave or a block has lanes; devices, multiplicities, two ports, per-neuron
+parameters, several instances; runs cut anywhere; networks just too large for
+one block beside them.  Snapshots pass both ways."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2007_14236_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _name(request):
+    print(f"\n[gpu-case] {request.node.nodeid}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def snn():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2007_14236_amd import snn as S
+    S.lib()
+    return S
+
+
+def brunel(n, k, seed=3, delay=("uniform", 0.1, 1.4), dmax=25, nu=260.0):
+    return W.brunel_lif(n=n, k=k, seed=seed, delay=delay, dmax=dmax, nu_ext=nu)
+
+
+def volley(n):
+    """Every neuron fires in the first step (above threshold), then again."""
+    sp = brunel(n, 30, delay=("uniform", 0.1, 1.0), dmax=10)
+    for p in sp["populations"]:
+        p["V0"] = np.full(p["n"], 25.0)
+    return sp
+
+
+def two_ports(n=1500, weights=(90.0, -200.0, 45.0)):
+    lif = dict(tau_m=10.0, C_m=250.0, E_L=-65.0, V_th=-50.0, V_reset=-65.0, t_ref=1.0, tau_syn=[0.5, 2.0])
+    pops = [dict(name=q, model="lif_exp", n=m, ports=2, params=dict(lif), V0=W.initial_v(7, m, -65.0, -50.0), I_e=420.0)
+            for q, m in (("A", n), ("B", n // 3))]
+    projs = [dict(src=s, tgt=t, K=40, weight=w, delay=("normal", 1.0, 0.5), port=p)
+             for s, w, p in (("A", weights[0], 0), ("B", weights[1], 1), ("A", weights[2], 1)) for t in ("A", "B")]
+    return dict(name="two_ports", dt=0.1, seed=8, dmax=30, populations=pops, projections=projs, poisson=[])
+
+
+def many_classes():
+    sp = two_ports()
+    sp["projections"][0]["weight_dist"] = dict(kind="normal", mean=90.0, sd=9.0, levels=40)
+    return sp
+
+
+def devices():
+    rng = np.random.default_rng(4)
+    times = [np.round(rng.uniform(0.1, 18.0, size=rng.integers(0, 15)), 1).tolist() for _ in range(70)]
+    times[0] = [0.1, 0.1, 2.0, 2.02, 1.98]
+    lif = dict(tau_m=20.0, C_m=250.0, E_L=0.0, V_th=20.0, V_reset=10.0, t_ref=2.0)
+    pops = [dict(name="G", model="spike_generator", n=70, ports=1, params={}, spike_times=times),
+            dict(name="R", model="parrot_neuron", n=70, ports=1, params={}),
+            dict(name="Q", model="parrot_neuron", n=30, ports=1, params={}),
+            dict(name="L", model="lif_delta", n=300, ports=1, params=dict(lif, V_th=np.linspace(18.0, 22.0, 300)),
+                 V0=np.linspace(0.0, 17.5, 300), I_e=300.0)]
+    projs = [dict(src="G", tgt="R", rule="one_to_one", weight=1.0, delay=("const", 0.7, 0.0), port=0),
+             dict(src="R", tgt="L", rule="fixed_outdegree", K=60, weight=2.5, delay=("uniform", 0.1, 2.0), port=0),
+             dict(src="Q", tgt="L", rule="fixed_indegree", K=5, weight=1.5, delay=("const", 0.3, 0.0), port=0),
+             dict(src="L", tgt="L", rule="fixed_indegree", K=20, weight=-0.4, delay=("normal", 1.0, 0.5), port=0)]
+    pois = [dict(tgt="Q", rate=500.0, n_inputs=8, weight=1.0, port=0)]
+    return dict(name="devices", dt=0.1, seed=8, dmax=40, populations=pops, projections=projs, poisson=pois)
+
+
+NETS = {f"n{n}": (lambda n=n: [brunel(n, max(1, min(n, 60)))]) for n in (5, 65, 1020, 1025, 2045)}
+NETS.update({
+    "two_a_thread_lds": lambda: [brunel(2040, 40, delay=("const", 0.4, 0.0), dmax=4)],
+    "one_delay": lambda: [brunel(800, 64, delay=("const", 0.1, 0.0), dmax=1)],
+    "63_delays": lambda: [brunel(300, 300, delay=("uniform", 0.1, 6.4), dmax=63)],
+    "long_rows": lambda: [brunel(700, 700, delay=("const", 0.5, 0.0), dmax=5)],
+    "volley_1500": lambda: [volley(1500)],
+    "volley_2040": lambda: [volley(2040)],
+    "two_ports": lambda: [two_ports(n=400)],
+    "two_ports_few": lambda: [two_ports(n=150)],
+    "many_classes": lambda: [many_classes()],
+    "devices": lambda: [devices()],
+    "instances": lambda: [brunel(300, 30, seed=s) for s in (3, 4, 5)],
+})
+
+
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_small_networks_bit_exact(snn, name):
+    specs, cuts = NETS[name](), (1, 6, 107, 110, 150)
+    g, d = snn.Net(specs), snn.Net(specs, delivery="direct")
+    assert g.counters()["delivery"] == 1
+    recs = []
+    for sp in specs:
+        o = O.OracleNet(sp, O.FP32SO)
+        rec = o.record_input(cuts[-1] + 1)
+        o.simulate(cuts[-1])
+        recs.append((o, rec))
+    done = 0
+    for n in cuts:
+        g.simulate(n - done)
+        d.simulate(n - done)
+        done = n
+        cg, cd = g.counters(), d.counters()
+        for k in ("steps", "spikes", "events", "pairs", "overflow"):
+            assert cg[k] == cd[k], (k, n)
+        for port in range(recs[0][1].shape[2]):
+            inp = g.get_input(port)
+            assert np.array_equal(inp, d.get_input(port)), n
+            if n < cuts[-1]:
+                for inst, (_, rec) in zip(g.instances, recs):
+                    assert np.array_equal(inp[inst["first"]:inst["first"] + inst["n"]], rec[n][:, port]), n
+    gs, gg, gm = g.spikes()
+    v = g.get_state("V_m").astype(np.float32)
+    for inst, (o, _) in zip(g.instances, recs):
+        a, b = inst["first"], inst["first"] + inst["n"]
+        sel = (gg >= a) & (gg < b)
+        for x, y in zip((gs[sel], gg[sel].astype(np.int64) - a, gm[sel]), o.spikes()):
+            assert np.array_equal(x.astype(np.int64), y.astype(np.int64))
+        assert np.array_equal(v[a:b], o.get_state("V_m").astype(np.float32))
+    for var, port in (("refr", 0), ("I_syn", 0), ("I_syn", recs[0][1].shape[2] - 1)):
+        assert np.array_equal(g.get_state(var, port=port), d.get_state(var, port=port))
+
+
+@pytest.mark.parametrize("name", ["n1020", "two_ports", "devices", "instances"])
+@pytest.mark.parametrize("src,dst", [("auto", "auto"), ("auto", "direct"), ("direct", "auto")])
+def test_small_snapshots(snn, name, src, dst):
+    """A snapshot goes on the same in either way of stepping, as do steps
+    profiled one by one."""
+    specs = NETS[name]()
+    a, b = snn.Net(specs, delivery=src), snn.Net(specs, delivery=dst)
+    a.simulate(53)
+    b.simulate(9)
+    b.restore(a.snapshot())
+    for x in (a, b):
+        x.simulate(20)
+        x.profile(7)
+        x.simulate(40)
+    for x, y in zip(a.spikes(53, 120), b.spikes(53, 120)):
+        assert np.array_equal(x, y)
+    ca, cb = a.counters(), b.counters()
+    assert all(ca[k] == cb[k] for k in ("steps", "spikes", "events", "pairs"))
+    assert np.array_equal(a.get_input(0), b.get_input(0))
+    assert np.array_equal(a.get_state("V_m"), b.get_state("V_m"))
