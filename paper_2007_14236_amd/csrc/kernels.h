@@ -34,9 +34,34 @@ hipError_t launch_masks(const uint32_t* cnt, uint32_t N, uint32_t D1, uint64_t* 
                         hipStream_t s);
 hipError_t launch_grp_off(const uint32_t* cnt, const uint64_t* off, const uint64_t* grp_ptr64, uint32_t N,
                           uint32_t D1, uint64_t* grp_off, uint32_t* grp_ptr32, hipStream_t s);
-// sort every group's payload ascending; groups longer than 16384 are listed in big[] (count in *nbig)
-hipError_t launch_segsort(const uint64_t* grp_off, uint64_t n_groups, uint32_t* payload, uint64_t* big,
-                          uint32_t* nbig, uint32_t big_cap, hipStream_t s);
+// Bins of consecutive sources that the synapses of a large network are drawn
+// into: sources [first[b], first[b + 1]), places off[b] .. off[b] + cap[b] of
+// rec (source in the bin << 6 | delay, payload), cnt[b] taken; *over is set when
+// one was full.  words: most (source, delay) counters of a bin.
+constexpr uint32_t kBinBuildMax = 4096;   // bins
+constexpr uint32_t kBinBuildWords = 24576;
+struct BinBuild {
+  uint32_t nbin, words;
+  const uint32_t* first;    // [nbin + 1]
+  const uint16_t* of_src;   // [N]
+  const uint64_t* off;      // [nbin]
+  const uint32_t* cap;      // [nbin]
+  uint32_t* cnt;            // [nbin], zeroed by the caller
+  uint32_t* over;
+  uint2* rec;
+};
+hipError_t launch_bin_gen(const ProjDev* projs, uint32_t nproj, uint64_t total_pairs, uint32_t dmax_cfg,
+                          const uint16_t* cls_of, const ProjW* pw, const uint32_t* pop_first, uint32_t npop,
+                          uint32_t cls_bits, const BinBuild& bb, hipStream_t s);
+hipError_t launch_bin_count(const BinBuild& bb, uint32_t D1, uint32_t* cnt, hipStream_t s);
+hipError_t launch_bin_place(const BinBuild& bb, uint32_t D1, const uint64_t* off, uint32_t* payload, hipStream_t s);
+// sort every group's payload ascending; longer: list of segsort_list entries
+// for groups beyond a wave's (*n_longer zeroed by the caller); groups longer
+// than 16384 are listed in big[] (count in *nbig)
+size_t segsort_list(uint64_t n_syn, uint64_t n_groups);
+hipError_t launch_segsort(const uint64_t* grp_off, uint64_t n_groups, uint32_t* payload, uint64_t* longer,
+                          uint32_t* n_longer, uint64_t list_cap, uint64_t* big, uint32_t* nbig, uint32_t big_cap,
+                          hipStream_t s);
 // Tile runs of every group (binned delivery with tile shift tsh): fill =
 // false counts them into cnt[g] (and sets *too_long for a group of
 // kRunMaxGroup synapses or more), fill = true writes them at run_desc[grp_run[g] ..].

@@ -33,6 +33,8 @@ constexpr uint32_t kGraphSteps = 100;
 constexpr int kNumParams = 16;  // SNN_P_TAU_M .. SNN_P_RK_HMIN
 constexpr uint64_t kChunkRing = 4096;  // >= drain interval + graph length
 constexpr uint64_t kBinnedMinSynapses = 500000000;  // default delivery: binned from this size on
+constexpr uint64_t kBinBuildMin = 1u << 20;        // build through bins of sources: synapses, at least
+constexpr uint64_t kBinBuildMax64 = 1ull << 31;    // ... at most (16 GiB of scratch)
 constexpr uint64_t kSmallSyn = 1u << 19;           // small networks: synapses, at most
 constexpr uint32_t kSmallPops = 16;                // ... populations
 constexpr uint64_t kPullMinMean = 4; // pulled delivery when the (group, tile) runs average this many synapses
@@ -1520,6 +1522,74 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
   return SNN_OK;
 }
 
+// Bins of consecutive sources for the build (kernels_build.hip), of about equal
+// numbers of synapses as the rules expect them, each with room for eight
+// standard deviations more.  bb.nbin stays 0 for small networks, sources that
+// do not fit the bins' counters, and where the scratch (8 bytes a synapse) is
+// too large or cannot be had; bufs: what was allocated.
+snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb, std::vector<void*>& bufs) {
+  if (total_syn < kBinBuildMin || total_syn > kBinBuildMax64) return SNN_OK;
+  const uint32_t N = net->N;
+  std::map<uint32_t, double> step;  // expected synapses per source, its changes along the gids
+  for (const HostProj& pr : net->projs) {
+    if (!pr.synapses()) continue;
+    const double per = (double)pr.synapses() / pr.src_n;
+    step[pr.src_first] += per;
+    step[pr.src_first + pr.src_n] -= per;
+  }
+  const uint32_t most = kBinBuildWords / D1;  // sources of a bin, at most
+  const double want = std::max((double)total_syn / 1000.0, 8192.0);
+  std::vector<uint32_t> first{0}, cap;
+  std::vector<uint64_t> off;
+  std::vector<uint16_t> of(N);
+  uint64_t places = 0;
+  double rate = 0.0, in_bin = 0.0;
+  auto close = [&](uint32_t end) {
+    const uint64_t c = (uint64_t)(in_bin + 8.0 * std::sqrt(in_bin) + 256.0);
+    off.push_back(places);
+    cap.push_back((uint32_t)std::min<uint64_t>(c, 0x7fffffffu));
+    places += c;
+    first.push_back(end);
+    in_bin = 0.0;
+  };
+  auto next = step.begin();
+  for (uint32_t i = 0; i < N; ++i) {
+    while (next != step.end() && next->first <= i) { rate += next->second; ++next; }
+    if (i > first.back() && (i - first.back() >= most || in_bin + 0.5 * rate > want)) close(i);
+    if (cap.size() >= kBinBuildMax) return SNN_OK;
+    of[i] = (uint16_t)cap.size();
+    in_bin += rate;
+  }
+  close(N);
+  bb.nbin = 0;
+  for (size_t b = 0; b < cap.size(); ++b) bb.words = std::max(bb.words, (first[b + 1] - first[b]) * D1);
+  uint32_t* d_first = dalloc<uint32_t>(net, first.size());
+  uint16_t* d_of = dalloc<uint16_t>(net, N);
+  uint64_t* d_off = dalloc<uint64_t>(net, off.size());
+  uint32_t* d_cap = dalloc<uint32_t>(net, cap.size());
+  uint32_t* d_cnt = dalloc<uint32_t>(net, cap.size() + 1);
+  uint2* d_rec = dalloc<uint2>(net, places);
+  bool ok = true;
+  for (void* p : {(void*)d_first, (void*)d_of, (void*)d_off, (void*)d_cap, (void*)d_cnt, (void*)d_rec}) {
+    if (p) bufs.push_back(p);
+    else ok = false;
+  }
+  if (!ok) {
+    for (void* p : bufs) dev_free(net, p);
+    bufs.clear();
+    return SNN_OK;
+  }
+  HIPCHK(net, copy_sync(net, d_first, first.data(), first.size() * 4, hipMemcpyHostToDevice));
+  HIPCHK(net, copy_sync(net, d_of, of.data(), (size_t)N * 2, hipMemcpyHostToDevice));
+  HIPCHK(net, copy_sync(net, d_off, off.data(), off.size() * 8, hipMemcpyHostToDevice));
+  HIPCHK(net, copy_sync(net, d_cap, cap.data(), cap.size() * 4, hipMemcpyHostToDevice));
+  HIPCHK(net, hipMemsetAsync(d_cnt, 0, (cap.size() + 1) * 4, net->stream));
+  bb.first = d_first; bb.of_src = d_of; bb.off = d_off; bb.cap = d_cap; bb.cnt = d_cnt; bb.over = d_cnt + cap.size();
+  bb.rec = d_rec;
+  bb.nbin = (uint32_t)cap.size();
+  return SNN_OK;
+}
+
 snn_status build_impl(snn_net* net) {
   snn_status st = enter(net);
   if (st) return st;
@@ -1923,8 +1993,28 @@ snn_status build_impl(snn_net* net) {
   if (!pd.empty()) HIPCHK(net, hipMemcpyAsync(d_proj, pd.data(), pd.size() * sizeof(ProjDev), hipMemcpyHostToDevice, s));
   HIPCHK(net, hipMemcpyAsync(d_clsof, cls_of.data(), cls_of.size() * 2, hipMemcpyHostToDevice, s));
   HIPCHK(net, hipMemcpyAsync(d_popfirst, pf.data(), npop * 4, hipMemcpyHostToDevice, s));
-  HIPCHK(net, hipMemsetAsync(d_cnt, 0, M * sizeof(uint32_t), s));
-  HIPCHK(net, launch_gen_count(d_proj, (uint32_t)pd.size(), total_pairs, dmax_cfg, D1, d_cnt, s));
+  uint32_t* d_pay; ALLOC(d_pay, uint32_t, std::max<uint64_t>(1, total_syn));
+  // large networks: drawn once into bins of sources, counted per bin
+  BinBuild bb{};
+  std::vector<void*> bin_bufs;
+  if (!(st = plan_bins(net, total_syn, D1, bb, bin_bufs)) && bb.nbin) {
+    HIPCHK(net, launch_bin_gen(d_proj, (uint32_t)pd.size(), total_pairs, dmax_cfg, d_clsof, d_pw, d_popfirst, npop,
+                               net->cls_bits, bb, s));
+    uint32_t over = 0;
+    HIPCHK(net, copy_sync(net, &over, bb.over, 4, hipMemcpyDeviceToHost));
+    if (over) {
+      for (void* b : bin_bufs) dev_free(net, b);
+      bin_bufs.clear();
+      bb.nbin = 0;
+    }
+  }
+  if (st) return st;
+  if (bb.nbin) {
+    HIPCHK(net, launch_bin_count(bb, D1, d_cnt, s));
+  } else {
+    HIPCHK(net, hipMemsetAsync(d_cnt, 0, M * sizeof(uint32_t), s));
+    HIPCHK(net, launch_gen_count(d_proj, (uint32_t)pd.size(), total_pairs, dmax_cfg, D1, d_cnt, s));
+  }
   HIPCHK(net, launch_scan_u32(d_cnt, M, d_off, d_tmp, s));
   HIPCHK(net, launch_masks(d_cnt, N, D1, d_mask, d_ng, s));
   HIPCHK(net, launch_scan_u64(d_ng, N, d_gp64, d_tmp, s));
@@ -1934,17 +2024,32 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, hipStreamSynchronize(s));
   if (S != total_syn) return fail(net, SNN_E_DEVICE, "synapse count mismatch (%llu vs %llu)",
                                   (unsigned long long)S, (unsigned long long)total_syn);
-  uint64_t* d_goff; ALLOC(d_goff, uint64_t, G + 1);
+  uint64_t* d_goff = dalloc<uint64_t>(net, G + 1);
+  if (!d_goff && bb.nbin) {  // the scratch of the bins may be what is missing
+    HIPCHK(net, hipStreamSynchronize(s));
+    for (void* b : bin_bufs) dev_free(net, b);
+    bin_bufs.clear();
+    bb.nbin = 0;
+    d_goff = dalloc<uint64_t>(net, G + 1);
+  }
+  if (!d_goff) return fail(net, SNN_E_NOMEM, "device allocation of %zu bytes failed", (size_t)(G + 1) * 8);
   HIPCHK(net, launch_grp_off(d_cnt, d_off, d_gp64, N, D1, d_goff, d_gp32, s));
   HIPCHK(net, hipMemcpyAsync(d_goff + G, &S, 8, hipMemcpyHostToDevice, s));
-  uint32_t* d_pay; ALLOC(d_pay, uint32_t, std::max<uint64_t>(1, S));
-  HIPCHK(net, launch_gen_scatter(d_proj, (uint32_t)pd.size(), total_pairs, dmax_cfg, D1, d_off, d_pay, d_clsof,
-                                 d_pw, d_popfirst, npop, net->cls_bits, s));
+  if (bb.nbin) {
+    HIPCHK(net, launch_bin_place(bb, D1, d_off, d_pay, s));
+    HIPCHK(net, hipStreamSynchronize(s));
+    for (void* b : bin_bufs) dev_free(net, b);
+  } else {
+    HIPCHK(net, launch_gen_scatter(d_proj, (uint32_t)pd.size(), total_pairs, dmax_cfg, D1, d_off, d_pay, d_clsof,
+                                   d_pw, d_popfirst, npop, net->cls_bits, s));
+  }
   const uint32_t big_cap = 4096;
   uint64_t* d_big; ALLOC(d_big, uint64_t, big_cap);
-  uint32_t* d_nbig; ALLOC(d_nbig, uint32_t, 1);
-  HIPCHK(net, hipMemsetAsync(d_nbig, 0, 4, s));
-  HIPCHK(net, launch_segsort(d_goff, G, d_pay, d_big, d_nbig, big_cap, s));
+  uint32_t* d_nbig; ALLOC(d_nbig, uint32_t, 2);
+  const size_t long_cap = segsort_list(S, G);
+  uint64_t* d_long; ALLOC(d_long, uint64_t, long_cap);
+  HIPCHK(net, hipMemsetAsync(d_nbig, 0, 8, s));
+  HIPCHK(net, launch_segsort(d_goff, G, d_pay, d_long, d_nbig + 1, long_cap, d_big, d_nbig, big_cap, s));
   uint32_t nbig = 0;
   HIPCHK(net, hipMemcpyAsync(&nbig, d_nbig, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(net, hipStreamSynchronize(s));
@@ -1961,7 +2066,7 @@ snn_status build_impl(snn_net* net) {
       HIPCHK(net, copy_sync(net, d_pay + be[0], seg.data(), seg.size() * 4, hipMemcpyHostToDevice));
     }
   }
-  dev_free(net, d_big); dev_free(net, d_nbig);
+  dev_free(net, d_big); dev_free(net, d_nbig); dev_free(net, d_long);
   dev_free(net, d_cnt); dev_free(net, d_off); dev_free(net, d_ng); dev_free(net, d_gp64); dev_free(net, d_tmp);
   dev_free(net, d_proj); dev_free(net, d_clsof); dev_free(net, d_popfirst);
   dev_free(net, d_wthr); dev_free(net, d_wcls); dev_free(net, d_lvl); dev_free(net, d_pw);
