@@ -249,30 +249,14 @@ __device__ __forceinline__ void adex_rhs(const AdexPar<P, kBeta>& pp, float Ie, 
   }
 }
 
-// One attempted substep of the Cash-Karp embedded 5(4) pair with the
-// step-size control of Press et al. (adaptive fifth-order Runge-Kutta,
-// Sec. 2.1): relative error against |y| + |h dy/dt| + 1 (state units; a floor
-// for variables at zero), shrink by 0.9 e^-1/4 (>= 0.1x) on failure, grow by
-// 0.9 e^-1/5 (<= 5x) on success; the last substep lands on the step end.  A
-// reset (V >= V_peak) is applied after every accepted substep.  t is the time
-// reached inside the step, it the attempts so far, mult the resets.  Returns
-// true when the step is complete (t = dt, or the attempt cap reached).  Each
-// stage state is y plus one fma per earlier stage (h folded into the
-// coefficients); the error ratio uses the hardware reciprocal (it only steers
-// the step size).
-template <int P, bool kBeta>
-__device__ __forceinline__ bool adex_substep(const AdexPar<P, kBeta>& pp, float* y, float& h, float& t, uint32_t& it,
-                                             uint32_t& mult, float Ie, uint32_t& nacc, uint32_t& nrej,
-                                             bool& capped) {
-  constexpr int NV = kAdexVars<P, kBeta>;
-  const float dt = pp.dt;
-  const float errcon = 1.89e-4f;  // (5 / 0.9)^-5
-  const float hmin = pp.hmin;
-  if (++it > kRkMaxIter) { capped = true; return true; }
-  bool last = false;
-  if (h >= dt - t) { h = dt - t; last = true; }
-  // stage coefficients times h: each stage state is y plus one fma per
-  // earlier stage, the newest last
+// One attempt of the Cash-Karp embedded 5(4) pair over NV variables: rhs(y, dy)
+// gives the derivatives, y5 the fifth-order solution; returns the largest
+// error ratio |err| / (|y| + |h dy/dt| + 1) of the variables.  Each stage state
+// is y plus one fma per earlier stage (h folded into the coefficients), the
+// newest last; the ratio uses the hardware reciprocal (it only steers the step
+// size).
+template <int NV, class Rhs>
+__device__ __forceinline__ float ck_attempt(const float* y, float h, Rhs rhs, float* y5) {
   const float a21 = h * (1.f / 5.f);
   const float a31 = h * (3.f / 40.f), a32 = h * (9.f / 40.f);
   const float a41 = h * (3.f / 10.f), a42 = h * (-9.f / 10.f), a43 = h * (6.f / 5.f);
@@ -285,31 +269,30 @@ __device__ __forceinline__ bool adex_substep(const AdexPar<P, kBeta>& pp, float*
               e4 = (float)(125.0 / 594.0 - 13525.0 / 55296.0), e5 = (float)(-277.0 / 14336.0),
               e6 = (float)(512.0 / 1771.0 - 0.25);
   float k1[NV], k2[NV], k3[NV], k4[NV], k5[NV], k6[NV], yt[NV];
-  adex_rhs<P, kBeta>(pp, Ie, y, k1);
+  rhs(y, k1);
 #pragma unroll
   for (int i = 0; i < NV; ++i) yt[i] = __builtin_fmaf(a21, k1[i], y[i]);
-  adex_rhs<P, kBeta>(pp, Ie, yt, k2);
+  rhs(yt, k2);
 #pragma unroll
   for (int i = 0; i < NV; ++i) yt[i] = __builtin_fmaf(a32, k2[i], __builtin_fmaf(a31, k1[i], y[i]));
-  adex_rhs<P, kBeta>(pp, Ie, yt, k3);
+  rhs(yt, k3);
 #pragma unroll
   for (int i = 0; i < NV; ++i)
     yt[i] = __builtin_fmaf(a43, k3[i], __builtin_fmaf(a42, k2[i], __builtin_fmaf(a41, k1[i], y[i])));
-  adex_rhs<P, kBeta>(pp, Ie, yt, k4);
+  rhs(yt, k4);
 #pragma unroll
   for (int i = 0; i < NV; ++i)
     yt[i] = __builtin_fmaf(a54, k4[i],
                            __builtin_fmaf(a53, k3[i], __builtin_fmaf(a52, k2[i], __builtin_fmaf(a51, k1[i], y[i]))));
-  adex_rhs<P, kBeta>(pp, Ie, yt, k5);
+  rhs(yt, k5);
 #pragma unroll
   for (int i = 0; i < NV; ++i)
     yt[i] = __builtin_fmaf(
         a65, k5[i],
         __builtin_fmaf(a64, k4[i],
                        __builtin_fmaf(a63, k3[i], __builtin_fmaf(a62, k2[i], __builtin_fmaf(a61, k1[i], y[i])))));
-  adex_rhs<P, kBeta>(pp, Ie, yt, k6);
+  rhs(yt, k6);
   float errmax = 0.f;
-  float y5[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     y5[i] = __builtin_fmaf(
@@ -320,23 +303,163 @@ __device__ __forceinline__ bool adex_substep(const AdexPar<P, kBeta>& pp, float*
     const float scale = __builtin_fmaf(h, fabsf(k1[i]), fabsf(y[i])) + 1.f;  // h > 0
     errmax = fmaxf(errmax, fabsf(err) * __builtin_amdgcn_rcpf(scale));
   }
-  errmax = errmax * pp.inv_eps;
-  if (errmax > 1.f && h > hmin) {
-    const float ht = 0.9f * h * __builtin_amdgcn_exp2f(-0.25f * __builtin_amdgcn_logf(errmax));
-    h = fmaxf(ht, 0.1f * h);
-    h = fmaxf(h, hmin);
+  return errmax;
+}
+
+// Step-size control after an attempt of size h with error ratio errmax over
+// the tolerance (Press et al.): shrink by 0.9 e^-1/4 (>= 0.1x) on failure, grow
+// by 0.9 e^-1/5 (<= 5x) on success, one logarithm and one power for either
+// (lanes of a wave take both).  Returns whether the attempt is accepted.
+__device__ __forceinline__ bool ck_control(float errmax, float hmin, float& h) {
+  const float errcon = 1.89e-4f;  // (5 / 0.9)^-5
+  const bool rej = errmax > 1.f && h > hmin;
+  const float z = 0.9f * h * __builtin_amdgcn_exp2f((rej ? -0.25f : -0.2f) * __builtin_amdgcn_logf(errmax));
+  const float hr = fmaxf(z, 0.1f * h), ha = errmax > errcon ? z : 5.f * h;
+  h = fmaxf(rej ? hr : ha, hmin);
+  return !rej;
+}
+
+// One attempted substep (adaptive fifth-order Runge-Kutta, Sec. 2.1); the last
+// substep lands on the step end.  A reset (V >= V_peak) is applied after every
+// accepted substep.  t is the time reached inside the step, it the attempts so
+// far, mult the resets.  Returns true when the step is complete (t = dt, or the
+// attempt cap reached).
+template <int P, bool kBeta>
+__device__ __forceinline__ bool adex_substep(const AdexPar<P, kBeta>& pp, float* y, float& h, float& t, uint32_t& it,
+                                             uint32_t& mult, float Ie, uint32_t& nacc, uint32_t& nrej,
+                                             bool& capped) {
+  constexpr int NV = kAdexVars<P, kBeta>;
+  const float dt = pp.dt;
+  if (++it > kRkMaxIter) { capped = true; return true; }
+  bool last = false;
+  if (h >= dt - t) { h = dt - t; last = true; }
+  float y5[NV];
+  const float errmax = ck_attempt<NV>(y, h, [&](const float* v, float* dv) { adex_rhs<P, kBeta>(pp, Ie, v, dv); }, y5);
+  const float tn = t + h;
+  if (!ck_control(errmax * pp.inv_eps, pp.hmin, h)) {
     ++nrej;
     return false;
   }
   ++nacc;
-  t = last ? dt : t + h;
+  t = last ? dt : tn;
 #pragma unroll
   for (int i = 0; i < NV; ++i) y[i] = y5[i];
-  const float hn =
-      fmaxf((errmax > errcon) ? 0.9f * h * __builtin_amdgcn_exp2f(-0.2f * __builtin_amdgcn_logf(errmax)) : 5.f * h, hmin);
   if (y[0] >= pp.V_peak) { y[0] = pp.V_r; y[1] += pp.b; ++mult; }
-  h = hn;
   return !(t < dt);
+}
+
+// ---- one neuron on four lanes ----
+// A neuron in its spike step takes ~100 attempts one after the other, and one
+// wave issues a vector instruction every four cycles, so an attempt costs its
+// instruction count.  A quad of lanes shares a neuron: lane 0 integrates V,
+// lane 1 w, lanes 2 and 3 the ports (p on lane 2 + p % 2); the stage sums, the
+// solution and the error of all variables are then one instruction stream.
+// Lane 0's right-hand side needs the others' stage values (quad permutations);
+// every operation on a variable and its order are those of adex_substep, so
+// the results are the same bit for bit.  Vector instructions of an attempt at
+// two ports (a transcendental counted four): 345 -> 262 exponential, 418 -> 302
+// beta; the step of 30,000 alpha-port neurons 109 -> 88 us, of 2,000 driven
+// AdEx neurons 69 -> 53 us.
+template <int K>
+__device__ __forceinline__ float quad_lane(float x) {  // lane K of the quad
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), K * 0x55, 0xf, 0xf, true));
+}
+template <int kPerm>
+__device__ __forceinline__ float quad_max(float x) {
+  return fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), kPerm, 0xf, 0xf, true)));
+}
+
+// One dt of a neuron whose parameters, state (y of adex_substep) and step size
+// every lane of its quad holds; at the end every lane holds the new ones.
+// Counts attempts on lane 0 of the quad.
+template <int P, bool kBeta>
+__device__ __forceinline__ void adex_quad_step(const AdexPar<P, kBeta>& pp, float* y, float& h, float Ie,
+                                               uint32_t& mult, uint32_t& nacc, uint32_t& nrej, bool& capped) {
+  constexpr int kG = (P + 1) / 2;              // ports of a port lane
+  constexpr int NV = kBeta ? 2 * kG : kG;      // variables of a lane: conductances, then rising variables
+  const uint32_t role = threadIdx.x & 3u;
+  const bool isV = role == 0, isW = role == 1;
+  const float dt = pp.dt;
+  float v[NV], T[kG], TR[kG];
+#pragma unroll
+  for (int j = 0; j < kG; ++j) {
+    v[j] = T[j] = TR[j] = 0.f;
+    if constexpr (kBeta) v[kG + j] = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int p = 2 * j + b;
+      if (p < P && role == 2u + b) {
+        v[j] = y[2 + p];
+        T[j] = pp.inv_tau_syn[p];
+        if constexpr (kBeta) { v[kG + j] = y[2 + P + p]; TR[j] = pp.inv_tau_rise[p]; }
+      }
+    }
+  }
+  if (isV) v[0] = y[0];
+  if (isW) { v[0] = y[1]; T[0] = pp.inv_tau_w; }
+  auto rhs = [&](const float* s, float* ds) {
+    const float V = quad_lane<0>(s[0]), w = quad_lane<1>(s[0]);
+    const float Vc = fminf(V, pp.V_peak);
+    const float d = V - pp.E_L;
+    const float ex = __builtin_amdgcn_exp2f((Vc - pp.V_T) * pp.k_exp);
+    float cur = Ie - w;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const float g = (p & 1) ? quad_lane<3>(s[p >> 1]) : quad_lane<2>(s[p >> 1]);
+      cur = __builtin_fmaf(-g, V - pp.E_rev[p], cur);
+    }
+    cur = __builtin_fmaf(-pp.g_L, d, cur);
+    // every lane has computed what only one needs: the empty asm keeps the
+    // selections below from becoming branches over it
+    float dV = __builtin_fmaf(pp.gLDT_C, ex, cur * pp.inv_C);
+    asm("" : "+v"(dV));
+    if constexpr (kBeta) {
+      float dw = __builtin_fmaf(pp.a, d, -s[0]) * T[0], dg = __builtin_fmaf(-s[0], T[0], s[kG]);
+      asm("" : "+v"(dw), "+v"(dg));
+      ds[0] = isV ? dV : (isW ? dw : dg);
+#pragma unroll
+      for (int j = 1; j < kG; ++j) ds[j] = __builtin_fmaf(-s[j], T[j], s[kG + j]);
+#pragma unroll
+      for (int j = 0; j < kG; ++j) ds[kG + j] = -s[kG + j] * TR[j];
+    } else {
+      float n = __builtin_fmaf(pp.a, d, -s[0]);
+      asm("" : "+v"(n));
+      n = isW ? n : -s[0];
+      ds[0] = isV ? dV : n * T[0];
+#pragma unroll
+      for (int j = 1; j < kG; ++j) ds[j] = -s[j] * T[j];
+    }
+  };
+  float t = 0.f;
+  for (uint32_t it = 0;;) {  // uniform over the quad
+    if (++it > kRkMaxIter) { capped = true; break; }
+    bool last = false;
+    if (h >= dt - t) { h = dt - t; last = true; }
+    float v5[NV];
+    float errmax = ck_attempt<NV>(v, h, rhs, v5);
+    errmax = quad_max<0x4E>(quad_max<0xB1>(errmax));
+    const float tn = t + h;
+    const bool ok = ck_control(errmax * pp.inv_eps, pp.hmin, h);
+    const bool spike = ok && quad_lane<0>(v5[0]) >= pp.V_peak;
+    nacc += (ok && isV) ? 1u : 0u;
+    nrej += (!ok && isV) ? 1u : 0u;
+    mult += spike ? 1u : 0u;
+    float reset = v5[0] + pp.b;
+    asm("" : "+v"(reset));
+    reset = isV ? pp.V_r : isW ? reset : v5[0];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = ok ? v5[j] : v[j];
+    v[0] = spike ? reset : v[0];
+    t = ok ? (last ? dt : tn) : t;
+    if (!(t < dt)) break;
+  }
+  y[0] = quad_lane<0>(v[0]);
+  y[1] = quad_lane<1>(v[0]);
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    y[2 + p] = (p & 1) ? quad_lane<3>(v[p >> 1]) : quad_lane<2>(v[p >> 1]);
+    if constexpr (kBeta) y[2 + P + p] = (p & 1) ? quad_lane<3>(v[kG + (p >> 1)]) : quad_lane<2>(v[kG + (p >> 1)]);
+  }
 }
 
 // One dt of the AdEx model: substeps until the step end, h carried to the
@@ -361,11 +484,12 @@ constexpr uint32_t kClsLds = 256; // weight classes cached in LDS by direct deli
 constexpr int kSelPerThread = kSelChunk / kB;
 static_assert(kTilePopLds <= kPoisLds, "a tile window's Poisson tables fit the LDS table");
 constexpr int kTileSubs = kTileAccWords / kB;  // most 256-neuron sub-blocks of a tile
-constexpr uint32_t kHotCap = 256;
+constexpr uint32_t kHotCap = 256;  // AdEx neurons of a tile queued ahead of the others
+constexpr uint32_t kHotQuads = 64; // ... and run on four lanes each
 // Delays of at least this many steps are delivered by the delivery blocks
 // (their spikes' records are complete when the step starts); delay-1 groups
 // by the blocks that emit the spikes, within the step.
-constexpr uint32_t kDlvMinDelay = 2;  // AdEx neurons of a tile queued ahead of the others
+constexpr uint32_t kDlvMinDelay = 2;
 
 // LDS of the selection: the selected (source, delay-group) records of one
 // chunk and their exclusive prefix of group sizes.
@@ -1357,10 +1481,13 @@ __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl
   }
   uint32_t nacc = 0, nrej = 0;
   bool capped = false, mover = false;
-  if (kAd != 0 && !kLif) {
-    // AdEx only: work queue over the tile's neurons; each lane holds its
-    // current neuron and has the next one's state already loaded, so the
-    // loads of a refill overlap the substeps of the current neuron
+  if constexpr (kAd != 0) {
+    // Neurons about to spike (V at or above V_T + 4 Delta_T) first, a quad of
+    // lanes each: up to 64 of them, 16 to a wave, the first 16 on a different
+    // wave in blocks b, b + 256, b + 512 (which dispatch places on one CU), at
+    // raised priority.  Those waves run nothing else meanwhile, since neuron
+    // loads and Poisson draws would stand between the substeps of the long
+    // chains; then they join the others.
     auto fetch = [&](uint32_t l, AdexItem<P, kAd == 2>& it) {
       int64_t a[kMaxPorts];
 #pragma unroll
@@ -1370,42 +1497,45 @@ __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl
     for (uint32_t l = threadIdx.x; l < nt; l += kB) {
       const uint32_t i = first + l;
       const PopDev& hp = pops[find_pop(pops, npop, i)];
-      const bool hot = nd.V[i] >= hp.V_T + 4.f * hp.Delta_T;
+      const bool hot = (!kLif || hp.model == kAdex || hp.model == kAdexBeta) && nd.V[i] >= hp.V_T + 4.f * hp.Delta_T;
       const uint64_t hb = __ballot(hot);
       if ((threadIdx.x & 31) == 0) sl.hot[l >> 5] = (uint32_t)(hb >> (threadIdx.x & 32));
       if (hot) {
         const uint32_t k = atomicAdd(&sl.hq_n, 1u);
-        if (k < kHotCap) sl.hq[k] = (uint16_t)l;
+        if (k < (kLif ? kHotQuads : kHotCap)) sl.hq[k] = (uint16_t)l;
         else atomicAnd(&sl.hot[l >> 5], ~(1u << (l & 31)));  // list full: taken in index order
       }
     }
     __syncthreads();
-    // The first 64 hot neurons go to one wave (a different one in blocks b,
-    // b + 256, b + 512, which dispatch places on one CU), lane by lane, and
-    // that wave runs only their substeps, at raised priority: a lane whose
-    // neuron is done idles, since refilling it would put neuron loads and
-    // Poisson draws between the substeps of the long chains.  Then the wave
-    // joins the others' queue.  Further hot neurons go to any wave first.
-    if ((threadIdx.x >> 6) == ((blockIdx.x >> 8) & 3u)) {
-      const uint32_t nh = min(min(sl.hq_n, kHotCap), 64u);
-      if (nh) {  // wave-uniform
-        __builtin_amdgcn_s_setprio(2);
-        uint32_t hl = ((threadIdx.x & 63u) < nh) ? (uint32_t)sl.hq[threadIdx.x & 63u] : nt;
-        AdexItem<P, kAd == 2> hw;
-        if (hl < nt) fetch(hl, hw);
-        while (hl < nt) {
-          if (adex_substep<P, kAd == 2>(hw.q, hw.y, hw.h, hw.t, hw.it, hw.mult, hw.Ie, nacc, nrej, capped)) {
-            sl.c.mk[hl] = (uint8_t)adex_store<P, kAd == 2>(nd, first + hl, hw, mover);
-            hl = nt;
-          }
-        }
-        __builtin_amdgcn_s_setprio(0);
+    const uint32_t nq = min(sl.hq_n, kHotQuads);
+    const uint32_t q0 = 16u * (((threadIdx.x >> 6) - (blockIdx.x >> 8)) & 3u);
+    if (q0 < nq) {  // wave-uniform
+      __builtin_amdgcn_s_setprio(2);
+      const uint32_t k = q0 + ((threadIdx.x & 63u) >> 2);
+      if (k < nq) {
+        const uint32_t l = sl.hq[k];
+        AdexItem<P, kAd == 2> w;
+        fetch(l, w);
+        adex_quad_step<P, kAd == 2>(w.q, w.y, w.h, w.Ie, w.mult, nacc, nrej, capped);
+        if ((threadIdx.x & 3u) == 0) sl.c.mk[l] = (uint8_t)adex_store<P, kAd == 2>(nd, first + l, w, mover);
       }
+      __builtin_amdgcn_s_setprio(0);
     }
+  }
+  if constexpr (kAd != 0 && !kLif) {
+    // AdEx only: work queue over the tile's other neurons; each lane holds its
+    // current neuron and has the next one's state already loaded, so the
+    // loads of a refill overlap the substeps of the current neuron
+    auto fetch = [&](uint32_t l, AdexItem<P, kAd == 2>& it) {
+      int64_t a[kMaxPorts];
+#pragma unroll
+      for (int p = 0; p < kMaxPorts; ++p) a[p] = (p < (int)PP) ? sl.u.acc[l * PP + p] : 0;
+      adex_load<P, kAd == 2>(nd, pops, npop, pthr, n, first + l, a, it);
+    };
     auto claim = [&]() -> uint32_t {
       const uint32_t nh = min(sl.hq_n, kHotCap);
-      if (nh > 64u) {
-        const uint32_t h = 64u + atomicAdd(&sl.hq_next2, 1u);
+      if (nh > kHotQuads) {
+        const uint32_t h = kHotQuads + atomicAdd(&sl.hq_next2, 1u);
         if (h < nh) return sl.hq[h];
       }
       for (;;) {
@@ -1434,6 +1564,7 @@ __device__ void tile_block(const NetDev& nd, uint64_t n, uint32_t t, TileLds& sl
     }
   } else {
     for (uint32_t loc = threadIdx.x; loc < nt; loc += kB) {
+      if (kAd != 0 && ((sl.hot[loc >> 5] >> (loc & 31)) & 1u)) continue;  // done by a quad
       int64_t a[kMaxPorts];
 #pragma unroll
       for (int p = 0; p < kMaxPorts; ++p) a[p] = (p < (int)PP) ? sl.u.acc[loc * PP + p] : 0;
