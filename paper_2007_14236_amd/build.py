@@ -14,8 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsnn.so")
 SOURCES = ["kernels_adex_beta.hip", "kernels_adex_beta_plastic.hip", "kernels_adex_exp.hip",
-           "kernels_adex_exp_plastic.hip", "kernels_step.hip", "kernels_pull.hip", "kernels_small.hip", "kernels_build.hip", "kernels_rec.hip",
-           "kernels_stdp.hip", "snn_api.cpp", "snn_server.cpp"]
+           "kernels_adex_exp_plastic.hip", "kernels_step.hip", "kernels_strip.hip", "kernels_pull.hip",
+           "kernels_small.hip", "kernels_build.hip", "kernels_rec.hip", "kernels_stdp.hip", "snn_api.cpp", "snn_server.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("SNN_OFFLOAD_ARCH", "gfx950")
 

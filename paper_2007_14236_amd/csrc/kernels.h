@@ -94,6 +94,13 @@ hipError_t launch_small_fold(const NetDev& nd, hipStream_t s);
 hipError_t launch_small_restore(const NetDev& nd, hipStream_t s);
 hipError_t launch_small_rows(const NetDev& nd, uint32_t* row, uint32_t* pay, hipStream_t s);
 size_t small_lds_bytes(const NetDev& nd);
+// Strips (kernels_strip.hip): one step, what a readback needs, what a restored
+// snapshot needs (spill cleared by the caller), the rows by (source, strip).
+constexpr uint32_t kStripPops = 16, kStripPois = 8;  // populations and Poisson tables, at most
+hipError_t launch_strip_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+hipError_t launch_strip_fold(const NetDev& nd, hipStream_t s);
+hipError_t launch_strip_restore(const NetDev& nd, hipStream_t s);
+hipError_t launch_strip_rows(const NetDev& nd, uint32_t* row, uint32_t* pay, uint32_t* deg, hipStream_t s);
 // The step kernels of networks with AdEx neurons: exponential ports only or
 // with beta ports, without or with plastic synapses (launch_step picks one).
 void launch_adex_exp(const NetDev& nd, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop, uint32_t rel,

@@ -341,17 +341,8 @@ __global__ void __launch_bounds__(kB) k_small_fold(NetDev nd) {
     return;
   }
   __shared__ uint64_t red[kB / 64];
-  uint64_t ev = 0, pr = 0;
-  for (uint32_t d = 1; d <= nd.dmax && d <= n; ++d) {  // spikes of step n - d: groups of delays above d
-    const uint32_t slot = (uint32_t)((n - d) % nd.R), cnt = nd.ring_cnt[slot];
-    for (uint32_t j = threadIdx.x; j < cnt; j += kB) {
-      const SpikeRec rec = nd.recent[(size_t)slot * nd.N + j];
-      const uint32_t all = rec.grp_ptr + (uint32_t)__popcll(rec.mask);
-      const uint32_t g = rec.grp_ptr + (uint32_t)__popcll(rec.mask & ((2ull << d) - 1ull));
-      pr += all - g;
-      ev += nd.grp_off[all] - nd.grp_off[g];
-    }
-  }
+  uint64_t ev, pr;
+  sent_pending<kB>(nd, n, ev, pr);
   ev = block_sum(ev, red);
   pr = block_sum(pr, red);
   if (threadIdx.x == 0) {

@@ -51,6 +51,7 @@ hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t
     launch_pull_step(nd, rel, s, start, stop);
     return hipGetLastError();
   }
+  if (nd.n_strips) return launch_strip_step(nd, rel, s, start, stop);
   if (adex || (nd.n_tiles && !nd.tile_win)) {  // or a tile overlaps more populations than its LDS window holds
     auto f = beta ? (plastic ? launch_adex_beta_plastic : launch_adex_beta)
                   : (plastic ? launch_adex_exp_plastic : launch_adex_exp);

@@ -36,6 +36,8 @@ constexpr uint64_t kBinnedMinSynapses = 500000000;  // default delivery: binned 
 constexpr uint64_t kBinBuildMin = 1u << 20;        // build through bins of sources: synapses, at least
 constexpr uint64_t kBinBuildMax64 = 1ull << 31;    // ... at most (16 GiB of scratch)
 constexpr uint64_t kSmallSyn = 1u << 19;           // small networks: synapses, at most
+constexpr uint32_t kStripGrid = 256;               // strips, about
+constexpr uint64_t kStripFree = 64ull << 20;       // ... bytes of their index, and of their spill, not weighed
 constexpr uint32_t kSmallPops = 16;                // ... populations
 constexpr uint64_t kPullMinMean = 4; // pulled delivery when the (group, tile) runs average this many synapses
 constexpr uint64_t kRunMinMean = 4;  // tile runs when groups average this many synapses per touched tile
@@ -505,11 +507,13 @@ void sort_raster(snn_net* net);
 snn_status build_graphs(snn_net* net);
 snn_status collect_samples(snn_net* net, uint64_t from, uint64_t to);
 
-// Pulled delivery and small networks: the next step's input as int64 sums in
-// acc, where the readback and the snapshot look for it (with pulled delivery
-// it is there already after a restore); small networks' delivery counters.
+// Pulled delivery, small networks and strips: the next step's input as
+// int64 sums in acc, where the readback and the snapshot look for it (with pulled
+// delivery it is there already after a restore); but for pulled delivery also the
+// delivery counters.
 snn_status pull_fold(snn_net* net) {
   if (net->nd.small_row) HIPCHK(net, launch_small_fold(net->nd, net->stream));
+  if (net->nd.n_strips) HIPCHK(net, launch_strip_fold(net->nd, net->stream));
   if (!net->nd.n_pull || net->acc_step == net->cur_step) return SNN_OK;
   HIPCHK(net, launch_pull_fold(net->nd, (uint32_t)(net->cur_step % kInBuf), net->stream));
   return SNN_OK;
@@ -1085,6 +1089,11 @@ snn_status snn_restore(snn_net* net, const void* buf, size_t size) {
     HIPCHK(net, launch_small_restore(net->nd, net->stream));
     HIPCHK(net, hipStreamSynchronize(net->stream));
   }
+  if (net->nd.n_strips) {  // likewise
+    HIPCHK(net, hipMemsetAsync(net->nd.strip_spill, 0, (size_t)net->nd.R * net->nd.N * net->nd.P * 8, net->stream));
+    HIPCHK(net, launch_strip_restore(net->nd, net->stream));
+    HIPCHK(net, hipStreamSynchronize(net->stream));
+  }
   if (net->nd.n_pull) {  // the next step takes its input from acc
     SpikeRec* tmp = dalloc<SpikeRec>(net, net->nd.N);
     if (!tmp) return fail(net, SNN_E_NOMEM, "allocation failed");
@@ -1409,6 +1418,53 @@ snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& p
   HIPCHK(net, launch_small_rows(x, d_row, d_pay, s));
   net->small_ring_bytes = ring * 4;
   nd = x;
+  return SNN_OK;
+}
+
+// Strips (kernels_strip.hip), for direct delivery of LIF networks that are not
+// small, without plastic synapses: about a strip per CU, of at least a wave.  They
+// were the faster way at every size tried (2,100 .. 450,000 neurons, 50 .. 4,000
+// synapses each; the figures stand there), so only memory draws the line: the row
+// index and the spill not beyond the synapses themselves (300,000 neurons with 30
+// synapses each: an index of 353 MB beside 36 MB), and the tables within a block's
+// LDS.  A list holds a quarter of the events that a volley of the whole network
+// brings; what lies beyond goes to the spill.
+snn_status build_strips(snn_net* net) {
+  const NetDev& nd = net->nd;
+  NetDev x = nd;
+  hipStream_t s = net->stream;
+  x.strip_n = std::min<uint32_t>(kStripN, std::max<uint32_t>(64, ((nd.N + kStripGrid - 1) / kStripGrid + 63) / 64 * 64));
+  const uint64_t S = (nd.N + x.strip_n - 1) / x.strip_n;
+  const uint64_t rows = (uint64_t)nd.N * (S + 1), spill = (uint64_t)nd.R * nd.N * nd.P;
+  if (S > kStripMax || !nd.n_syn || nd.n_syn >> 32 || nd.npop > kStripPops || nd.npois > kStripPois) return SNN_OK;
+  if (rows * 4 > std::max<uint64_t>(kStripFree, nd.n_syn * 4) || spill * 8 > std::max<uint64_t>(kStripFree, nd.n_syn * 4))
+    return SNN_OK;
+  x.n_strips = (uint32_t)S;
+  const double run = (double)nd.n_syn / (double)(nd.N * S);  // synapses of a source onto a strip, mean
+  x.strip_lanes = 0;
+  while (x.strip_lanes < 6 && (double)(1u << x.strip_lanes) < run + 2.0 * std::sqrt(run)) ++x.strip_lanes;
+  x.strip_cap = (uint32_t)std::max<uint64_t>(256, nd.n_syn / (S * nd.R * 4));
+  const size_t old = net->allocs.size();
+  uint32_t* d_row = dalloc<uint32_t>(net, rows);
+  uint32_t* d_pay = dalloc<uint32_t>(net, nd.n_syn);
+  uint32_t* d_deg = dalloc<uint32_t>(net, nd.N);
+  x.strip_list = dalloc<uint32_t>(net, S * nd.R * x.strip_cap);
+  x.strip_cur = dalloc<uint32_t>(net, S * nd.R);
+  x.strip_spill = dalloc<int64_t>(net, spill);
+  x.strip_ovf = dalloc<uint64_t>(net, S);
+  x.strip_spk = dalloc<uint32_t>(net, (size_t)2 * nd.N);
+  x.strip_cnt = dalloc<uint32_t>(net, 4);
+  x.strip_sent = dalloc<uint64_t>(net, 2);
+  x.strip_pois = dalloc<uint8_t>(net, nd.N);
+  if (!d_row || !d_pay || !d_deg || !x.strip_list || !x.strip_cur || !x.strip_spill || !x.strip_ovf || !x.strip_spk ||
+      !x.strip_cnt || !x.strip_sent || !x.strip_pois) {
+    while (net->allocs.size() > old) dev_free(net, net->allocs.back().p);
+    return SNN_OK;
+  }
+  HIPCHK(net, hipMemsetAsync(x.strip_spill, 0, spill * 8, s));
+  HIPCHK(net, launch_strip_rows(x, d_row, d_pay, d_deg, s));
+  x.strip_row = d_row; x.strip_pay = d_pay; x.strip_deg = d_deg;
+  net->nd = x;
   return SNN_OK;
 }
 
@@ -2351,7 +2407,7 @@ snn_status build_impl(snn_net* net) {
 
   net->unit_shift = nd.n_tiles ? nd.tile_shift : 6u;
   if (!nd.n_tiles && !net->has_adex && !nd.n_rules && !(net->cfg.flags & SNN_F_DELIVERY_DIRECT) &&
-      (st = build_small(net, pop_cls)))
+      ((st = build_small(net, pop_cls)) || (!nd.small_row && (st = build_strips(net)))))
     return st;
 
   // ---- spike buffers ----
@@ -2385,6 +2441,7 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, hipMemsetAsync(nd.blk_stats, 0, (size_t)kBlkStats * nd.nblk_upd * 8, s));
   ALLOC(nd.ctrl, Ctrl, 1);
   HIPCHK(net, hipMemsetAsync(nd.ctrl, 0, sizeof(Ctrl), s));
+  if (nd.n_strips) HIPCHK(net, launch_strip_restore(nd, s));
   net->pinned_words = 0;
   HIPCHK(net, hipHostMalloc((void**)&net->pin_cb, kChunkRing * 8, hipHostMallocDefault));
   HIPCHK(net, hipHostMalloc((void**)&net->pin_rc, (size_t)nd.R * 4, hipHostMallocDefault));
@@ -2562,7 +2619,7 @@ snn_status snn_get_counters(snn_net* net, snn_counters* out) {
   if (!net->built) return SNN_OK;
   snn_status st = enter(net);
   if (st) return st;
-  if (net->nd.small_row && (st = pull_fold(net))) return st;
+  if ((net->nd.small_row || net->nd.n_strips) && (st = pull_fold(net))) return st;
   HIPCHK(net, hipStreamSynchronize(net->stream));
   Ctrl c;
   HIPCHK(net, copy_sync(net, &c, net->nd.ctrl, sizeof c, hipMemcpyDeviceToHost));

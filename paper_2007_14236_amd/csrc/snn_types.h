@@ -168,6 +168,11 @@ constexpr uint32_t kPullGrid = 256;        // a block of k_pull on each CU
 // Small networks (small_row set): all steps of a launch in one block.
 constexpr uint32_t kSmallN = 2048;         // neurons, at most: two a thread
 constexpr size_t kSmallLds = 160 * 1024;   // LDS of a block
+// Strips (n_strips set): a neuron a thread, and the strips of a network.
+constexpr uint32_t kStripN = 1024;
+constexpr uint32_t kStripMax = 512;
+constexpr int kStripDelayShift = 10;       // synapse of a strip's row: local target << 16 | delay << 10 | class
+constexpr int kStripLocalShift = 16;
 // An instance's slices [s0, s0 + ns), tiles [t0, t0 + nt), first group and
 // synapse, and where its 16-bit synapses (an even place) and its run index
 // start: row k of group g is pull_row[row0 + (g - g0) * nt + k], counted from
@@ -279,6 +284,25 @@ struct NetDev {
   uint32_t* small_ring;
   uint8_t* small_pois;
   uint64_t* small_sent;        // [2]
+  // strips (n_strips of strip_n neurons; 0: off): source s's synapses onto strip
+  // t, strip_pay[strip_row[s][t] .. strip_row[s][t + 1]) (target in the strip, delay,
+  // class); the events (as in a bin) that reach strip t in step slot r,
+  // strip_list[t][r][0 .. strip_cur[t][r]); sums of those that found it full,
+  // strip_spill[R][N][P], and the strip's slots that hold some; the spikes of even
+  // and odd steps, strip_spk[2][N], and their counts by step mod 4; pairs and
+  // events that a restore found delivered and on their way
+  uint32_t n_strips, strip_n, strip_lanes, strip_cap;
+  const uint32_t* strip_row;   // [N][n_strips + 1]
+  const uint32_t* strip_pay;
+  const uint32_t* strip_deg;   // [N] synapses of a source
+  uint32_t* strip_list;
+  uint32_t* strip_cur;
+  int64_t* strip_spill;
+  uint64_t* strip_ovf;         // [n_strips]
+  uint32_t* strip_spk;
+  uint32_t* strip_cnt;         // [4]
+  uint64_t* strip_sent;        // [2]
+  uint8_t* strip_pois;         // [N] Poisson counts of the next step
 };
 
 }  // namespace snn

@@ -106,8 +106,21 @@ __device__ __forceinline__ uint64_t block_max(uint64_t v, uint64_t* lds) {
 __device__ __forceinline__ uint32_t poisson_draw(const uint64_t* thr, uint64_t seed, uint32_t gid, uint64_t n) {
   const U64x4 r = philox4x64_10(gid, n, kTagPoisson, 0, seed, 0);
   const uint64_t u = r.w[0] >> 32;
+  // eight thresholds at a time, their reads together: the first one above u
+  // ends the count, whatever lies behind it
   uint32_t k = 0;
-  while (k < kPoisKmax - 1 && u >= thr[k]) ++k;
+  for (;;) {
+    bool all = true;
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      all = u >= thr[k + q] && all;
+      c += all ? 1u : 0u;
+    }
+    k += c;
+    if (c < 8 || k >= (uint32_t)kPoisKmax) break;
+  }
+  if (k > (uint32_t)kPoisKmax - 1) k = kPoisKmax - 1;
   return k;
 }
 
@@ -121,7 +134,8 @@ struct LifK {
   int32_t n_ref;
 };
 
-__device__ __forceinline__ LifK lif_consts(const NetDev& nd, const PopDev& pp, uint32_t i) {
+template <class ND>
+__device__ __forceinline__ LifK lif_consts(const ND& nd, const PopDev& pp, uint32_t i) {
   LifK k;
   if (pp.per_neuron) {
     const NeuronLif& c = nd.nlif[i];
@@ -1164,18 +1178,19 @@ __device__ __forceinline__ uint32_t neuron_step(const NetDev& nd, const PopDev* 
   return m;
 }
 
+template <int kT = kB>
 __device__ __forceinline__ void load_tables(const NetDev& nd, PopDev* spops, uint32_t pop_cap, uint64_t* sthr,
                                             const PopDev*& pops, const uint64_t*& pthr) {
   const bool lds_pops = nd.npop <= pop_cap;
   const bool lds_thr = nd.npois <= kPoisLds;
   if (lds_pops) {
     const uint32_t words = nd.npop * (uint32_t)(sizeof(PopDev) / 4);
-    for (uint32_t w = threadIdx.x; w < words; w += kB)
+    for (uint32_t w = threadIdx.x; w < words; w += kT)
       reinterpret_cast<uint32_t*>(spops)[w] = reinterpret_cast<const uint32_t*>(nd.pops)[w];
   }
   if (lds_thr) {
     const uint32_t len = nd.pois_len;
-    for (uint32_t w = threadIdx.x; w < nd.npois * len; w += kB) {
+    for (uint32_t w = threadIdx.x; w < nd.npois * len; w += kT) {
       const uint32_t q = w / len, k = w - q * len;
       sthr[q * kPoisKmax + k] = nd.pois_thr[q * kPoisKmax + k];
     }
@@ -1265,6 +1280,23 @@ __device__ __forceinline__ void emit_spike(const NetDev& nd, uint64_t n, uint64_
   r.grp_ptr = grp_ptr;
   r.mask = mask;
   nd.recent[(size_t)(n % nd.R) * nd.N + pos] = r;
+}
+
+// A thread's share of the pairs and events that arrive after step n, the next
+// to run: of the spikes of step n - d the groups of delays above d.
+template <int kT>
+__device__ __forceinline__ void sent_pending(const NetDev& nd, uint64_t n, uint64_t& ev, uint64_t& pr) {
+  ev = pr = 0;
+  for (uint32_t d = 1; d <= nd.dmax && d <= n; ++d) {
+    const uint32_t slot = (uint32_t)((n - d) % nd.R), cnt = min(nd.ring_cnt[slot], nd.N);
+    for (uint32_t j = threadIdx.x; j < cnt; j += kT) {
+      const SpikeRec rec = nd.recent[(size_t)slot * nd.N + j];
+      const uint32_t all = rec.grp_ptr + (uint32_t)__popcll(rec.mask);
+      const uint32_t g = rec.grp_ptr + (uint32_t)__popcll(rec.mask & ((2ull << d) - 1ull));
+      pr += all - g;
+      ev += nd.grp_off[all] - nd.grp_off[g];
+    }
+  }
 }
 
 // Direct-delivery update block: 256 neurons, input from acc[n % 2] (read and

@@ -1,0 +1,159 @@
+"""GPU parity of strips (a block takes the input of its own neurons, through lists
+of events by arrival step): rasters, potentials, pending inputs and counters
+bit-exact against the oracle and against delivery by device atomics.
+Sizes where it can go wrong: a strip of one neuron, one delay of 1 or 2, all
+delays to 63, rows shorter than a strip's share of lanes and hundreds long, more
+spikes in a step than a block has lanes, lists that overflow, strips of two waves and more, multiplicities, three and four
+ports, per-neuron parameters, hundreds of weight classes, several instances; runs
+cut anywhere.  Snapshots pass both ways, spikes in flight included."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2007_14236_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _name(request):
+    print(f"\n[gpu-case] {request.node.nodeid}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def snn():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2007_14236_amd import snn as S
+    S.lib()
+    return S
+
+
+def brunel(n, k, seed=3, delay=("uniform", 0.1, 1.4), dmax=25, nu=260.0):
+    return W.brunel_lif(n=n, k=k, seed=seed, delay=delay, dmax=dmax, nu_ext=nu)
+
+
+def volley(n, k):
+    """Every neuron fires in the first step (above threshold), then again."""
+    sp = brunel(n, k, delay=("uniform", 0.1, 1.0), dmax=10)
+    for p in sp["populations"]:
+        p["V0"] = np.full(p["n"], 25.0)
+    return sp
+
+
+def ports(np_, n=2500, levels=0):
+    lif = dict(tau_m=10.0, C_m=250.0, E_L=-65.0, V_th=-50.0, V_reset=-65.0, t_ref=1.0,
+               tau_syn=[0.5, 2.0, 1.0, 3.0][:np_])
+    pops = [dict(name=q, model="lif_exp", n=m, ports=np_, params=dict(lif), V0=W.initial_v(7, m, -65.0, -50.0), I_e=420.0)
+            for q, m in (("A", n), ("B", n // 3))]
+    projs = [dict(src=s, tgt=t, K=30, weight=w, delay=("normal", 1.0, 0.5), port=p % np_)
+             for s, w, p in (("A", 90.0, 0), ("B", -200.0, 1), ("A", 45.0, 2), ("B", -30.0, 3)) for t in ("A", "B")]
+    if levels:
+        for j, p in enumerate(projs[:2]):
+            p["weight_dist"] = dict(kind="normal", mean=90.0 + j, sd=9.0, levels=levels)
+    return dict(name="ports", dt=0.1, seed=8, dmax=30, populations=pops, projections=projs, poisson=[])
+
+
+def devices():
+    rng = np.random.default_rng(4)
+    times = [np.round(rng.uniform(0.1, 18.0, size=rng.integers(0, 15)), 1).tolist() for _ in range(70)]
+    times[0] = [0.1, 0.1, 2.0, 2.02, 1.98]
+    lif = dict(tau_m=20.0, C_m=250.0, E_L=0.0, V_th=20.0, V_reset=10.0, t_ref=2.0)
+    n = 2200
+    pops = [dict(name="G", model="spike_generator", n=70, ports=1, params={}, spike_times=times),
+            dict(name="R", model="parrot_neuron", n=70, ports=1, params={}),
+            dict(name="Q", model="parrot_neuron", n=30, ports=1, params={}),
+            dict(name="L", model="lif_delta", n=n, ports=1, params=dict(lif, V_th=np.linspace(18.0, 22.0, n)),
+                 V0=np.linspace(0.0, 17.5, n), I_e=300.0)]
+    projs = [dict(src="G", tgt="R", rule="one_to_one", weight=1.0, delay=("const", 0.7, 0.0), port=0),
+             dict(src="R", tgt="L", rule="fixed_outdegree", K=300, weight=2.5, delay=("uniform", 0.1, 2.0), port=0),
+             dict(src="Q", tgt="L", rule="fixed_indegree", K=5, weight=1.5, delay=("const", 0.3, 0.0), port=0),
+             dict(src="L", tgt="L", rule="fixed_indegree", K=20, weight=-0.4, delay=("normal", 1.0, 0.5), port=0)]
+    pois = [dict(tgt="Q", rate=500.0, n_inputs=8, weight=1.0, port=0)]
+    return dict(name="devices", dt=0.1, seed=8, dmax=40, populations=pops, projections=projs, poisson=pois)
+
+
+NETS = {
+    "n2049": lambda: ([brunel(2049, 3)], {}),
+    "strips_of_128": lambda: ([brunel(20011, 60)], {}),
+    "strips_of_320": lambda: ([brunel(70001, 20)], {}),
+    "delay_1": lambda: ([brunel(2300, 70, delay=("const", 0.1, 0.0), dmax=1)], {}),
+    "delay_2": lambda: ([brunel(2300, 70, delay=("const", 0.2, 0.0), dmax=2)], {}),
+    "delays_1_2": lambda: ([brunel(2300, 70, delay=("uniform", 0.1, 0.2), dmax=2)], {}),
+    "63_delays": lambda: ([brunel(2100, 200, delay=("uniform", 0.1, 6.4), dmax=63)], {}),
+    "long_rows": lambda: ([brunel(2100, 2100, delay=("uniform", 0.1, 3.0), dmax=30, nu=150.0)], {}),
+    "volley": lambda: ([volley(6000, 40)], {}),
+    "volley_overflows": lambda: ([volley(3000, 400)], {}),
+    "one_block": lambda: ([volley(2600, 30)], dict(delivery_blocks=1)),
+    "three_ports": lambda: ([ports(3)], {}),
+    "four_ports": lambda: ([ports(4)], {}),
+    "classes": lambda: ([ports(2, levels=100)], {}),
+    "devices": lambda: ([devices()], {}),
+    "instances": lambda: ([brunel(900, 30, seed=s) for s in (3, 4, 5)], {}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_strips_bit_exact(snn, name):
+    (specs, kw), cuts = NETS[name](), (1, 2, 9, 107, 110, 150)
+    g, d = snn.Net(specs, **kw), snn.Net(specs, delivery="direct", **kw)
+    assert g.counters()["delivery"] == 1
+    recs = []
+    for sp in specs:
+        o = O.OracleNet(sp, O.FP32SO)
+        rec = o.record_input(cuts[-1] + 1)
+        o.simulate(cuts[-1])
+        recs.append((o, rec))
+    done = 0
+    for n in cuts:
+        g.simulate(n - done)
+        d.simulate(n - done)
+        done = n
+        cg, cd = g.counters(), d.counters()
+        for k in ("steps", "spikes", "events", "pairs", "overflow"):
+            assert cg[k] == cd[k], (k, n)
+        for port in range(recs[0][1].shape[2]):
+            inp = g.get_input(port)
+            assert np.array_equal(inp, d.get_input(port)), n
+            if n < cuts[-1]:
+                for inst, (_, rec) in zip(g.instances, recs):
+                    assert np.array_equal(inp[inst["first"]:inst["first"] + inst["n"]], rec[n][:, port]), n
+    gs, gg, gm = g.spikes()
+    assert len(gs) > 0
+    v = g.get_state("V_m").astype(np.float32)
+    for inst, (o, _) in zip(g.instances, recs):
+        a, b = inst["first"], inst["first"] + inst["n"]
+        sel = (gg >= a) & (gg < b)
+        for x, y in zip((gs[sel], gg[sel].astype(np.int64) - a, gm[sel]), o.spikes()):
+            assert np.array_equal(x.astype(np.int64), y.astype(np.int64))
+        assert np.array_equal(v[a:b], o.get_state("V_m").astype(np.float32))
+    for var, port in (("refr", 0), ("I_syn", 0), ("I_syn", recs[0][1].shape[2] - 1)):
+        assert np.array_equal(g.get_state(var, port=port), d.get_state(var, port=port))
+
+
+@pytest.mark.parametrize("name", ["delays_1_2", "63_delays", "devices", "instances"])
+@pytest.mark.parametrize("src,dst", [("auto", "auto"), ("auto", "direct"), ("direct", "auto")])
+def test_strip_snapshots(snn, name, src, dst):
+    """A snapshot goes on the same in either delivery, also over a network that
+    has run further on other spikes, as do steps profiled one by one."""
+    specs, kw = NETS[name]()
+    a, b = snn.Net(specs, delivery=src, **kw), snn.Net(specs, delivery=dst, **kw)
+    a.simulate(53)
+    b.simulate(54)
+    b.set_state("V_m", 0, np.full(b.N, -3.0))
+    b.simulate(1)
+    b.restore(a.snapshot())
+    for x in (a, b):
+        x.simulate(20)
+        x.profile(7)
+        x.simulate(40)
+    for x, y in zip(a.spikes(53, 120), b.spikes(53, 120)):
+        assert np.array_equal(x, y)
+    ca, cb = a.counters(), b.counters()
+    assert all(ca[k] == cb[k] for k in ("steps", "spikes", "events", "pairs"))
+    assert np.array_equal(a.get_input(0), b.get_input(0))
+    assert np.array_equal(a.get_state("V_m"), b.get_state("V_m"))
