@@ -31,7 +31,7 @@ size_t scan_tmp_words(uint64_t n);
 hipError_t launch_scan_u32(const uint32_t* in, uint64_t n, uint64_t* out, uint64_t* tmp, hipStream_t s);
 hipError_t launch_scan_u64(const uint64_t* in, uint64_t n, uint64_t* out, uint64_t* tmp, hipStream_t s);
 hipError_t launch_masks(const uint32_t* cnt, uint32_t N, uint32_t D1, uint64_t* mask, uint64_t* ngroups,
-                        hipStream_t s);
+                        uint32_t* longest, hipStream_t s);  // longest (or null): synapses of a source, at most
 hipError_t launch_grp_off(const uint32_t* cnt, const uint64_t* off, const uint64_t* grp_ptr64, uint32_t N,
                           uint32_t D1, uint64_t* grp_off, uint32_t* grp_ptr32, hipStream_t s);
 // Bins of consecutive sources that the synapses of a large network are drawn
@@ -48,6 +48,7 @@ struct BinBuild {
   const uint32_t* cap;      // [nbin]
   uint32_t* cnt;            // [nbin], zeroed by the caller
   uint32_t* over;
+  uint32_t* longest;        // longest row, from launch_masks
   uint2* rec;
 };
 hipError_t launch_bin_gen(const ProjDev* projs, uint32_t nproj, uint64_t total_pairs, uint32_t dmax_cfg,
@@ -58,10 +59,21 @@ hipError_t launch_bin_place(const BinBuild& bb, uint32_t D1, const uint64_t* off
 // sort every group's payload ascending; longer: list of segsort_list entries
 // for groups beyond a wave's (*n_longer zeroed by the caller); groups longer
 // than 16384 are listed in big[] (count in *nbig)
+// rows: the words are in place by source only (launch_bin_rows), their delays in
+// del; otherwise (del null) by group.
+struct RowSort {
+  const uint8_t* del = nullptr;
+  const uint64_t* off = nullptr;      // [N * D1 + 1] as for launch_bin_place
+  const uint32_t* grp_ptr = nullptr;  // [N + 1]
+  uint32_t D1 = 0, N = 0, longest = 0;
+};
+bool row_sort_fits(const BinBuild& bb, uint32_t D1, uint32_t longest, uint64_t mean);
+hipError_t launch_bin_rows(const BinBuild& bb, uint32_t D1, const uint64_t* off, uint32_t* payload, uint8_t* del,
+                           hipStream_t s);
 size_t segsort_list(uint64_t n_syn, uint64_t n_groups);
 hipError_t launch_segsort(const uint64_t* grp_off, uint64_t n_groups, uint32_t* payload, uint64_t* longer,
                           uint32_t* n_longer, uint64_t list_cap, uint64_t* big, uint32_t* nbig, uint32_t big_cap,
-                          hipStream_t s);
+                          const RowSort& rows, hipStream_t s);
 // Tile runs of every group (binned delivery with tile shift tsh): fill =
 // false counts them into cnt[g] (and sets *too_long for a group of
 // kRunMaxGroup synapses or more), fill = true writes them at run_desc[grp_run[g] ..].

@@ -286,6 +286,78 @@ __global__ void __launch_bounds__(kBT) k_bin_place(BinBuild bb, uint32_t D1, con
   }
 }
 
+// Block = one bin: its synapses brought to their sources' rows (words into
+// payload, delays into del), for k_row_sort to order.  kRowChunk of them at a
+// time are put in source order in LDS, so that a source's are written side by
+// side: placed at their (source, delay) groups at once, each by itself, 3.0 10^8
+// took 4.8 ms (every 4-byte store a line of its own), and the sorting of the
+// // groups, a wave each behind two dependent reads, another 2.7; now 1.1 here and
+// 2.8 in k_row_sort.
+constexpr int kRowItems = 8;
+constexpr uint32_t kRowChunk = kRowItems * kBT;
+__global__ void __launch_bounds__(kBT) k_bin_rows(BinBuild bb, uint32_t D1, const uint64_t* __restrict__ off,
+                                                  uint32_t* __restrict__ payload, uint8_t* __restrict__ del) {
+  extern __shared__ uint32_t sbuf[];
+  uint32_t* word = sbuf;                                            // [kRowChunk]
+  uint16_t* src = reinterpret_cast<uint16_t*>(word + kRowChunk);    // [kRowChunk]
+  uint8_t* dly = reinterpret_cast<uint8_t*>(src + kRowChunk);       // [kRowChunk]
+  uint32_t* cur = reinterpret_cast<uint32_t*>(dly + kRowChunk);     // [kBT] next place of a source
+  uint32_t* cnt = cur + kBT;                                        // [kBT] the chunk's synapses of a source
+  uint32_t* first = cnt + kBT;                                      // [kBT] ... and their place in the chunk
+  __shared__ uint32_t wsum[kBT / 64];
+  const uint32_t b = blockIdx.x, f = bb.first[b], ns = bb.first[b + 1] - f, tid = threadIdx.x;
+  const uint64_t base = off[(uint64_t)f * D1];
+  if (tid < ns) cur[tid] = (uint32_t)(off[(uint64_t)(f + tid) * D1] - base);
+  const uint2* rec = bb.rec + bb.off[b];
+  const uint32_t n = bb.cnt[b];
+  for (uint32_t j0 = 0; j0 < n; j0 += kRowChunk) {  // block-uniform
+    const uint32_t m = min(kRowChunk, n - j0);
+    uint2 r[kRowItems];
+    uint32_t rank[kRowItems];
+#pragma unroll
+    for (int u = 0; u < kRowItems; ++u) {
+      const uint32_t j = u * kBT + tid;
+      r[u] = j < m ? rec[j0 + j] : make_uint2(0u, 0u);
+    }
+    cnt[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRowItems; ++u)
+      if (u * kBT + tid < m) rank[u] = atomicAdd(&cnt[r[u].x >> 6], 1u);
+    __syncthreads();
+    const uint32_t c = cnt[tid];
+    uint32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(incl, o, 64);
+      if ((tid & 63) >= (uint32_t)o) incl += y;
+    }
+    if ((tid & 63) == 63) wsum[tid >> 6] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t w = 0; w < tid >> 6; ++w) before += wsum[w];
+    first[tid] = before + incl - c;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRowItems; ++u)
+      if (u * kBT + tid < m) {
+        const uint32_t s = r[u].x >> 6, at = first[s] + rank[u];
+        word[at] = r[u].y;
+        src[at] = (uint16_t)s;
+        dly[at] = (uint8_t)(r[u].x & 63u);
+      }
+    __syncthreads();
+    for (uint32_t j = tid; j < m; j += kBT) {
+      const uint32_t s = src[j];
+      const uint64_t at = base + cur[s] + (j - first[s]);
+      payload[at] = word[j];
+      del[at] = dly[j];
+    }
+    __syncthreads();
+    if (tid < ns) cur[tid] += c;
+  }
+}
+
 uint32_t grid_for(uint64_t work, uint32_t per_block, uint32_t cap) {
   uint64_t g = (work + per_block - 1) / per_block;
   if (g < 1) g = 1;
@@ -388,14 +460,17 @@ hipError_t scan_impl(const T* in, uint64_t n, uint64_t* out, uint64_t* tmp, hipS
 }
 
 __global__ void __launch_bounds__(kB) k_masks(const uint32_t* __restrict__ cnt, uint32_t N, uint32_t D1, uint64_t* mask,
-                                              uint64_t* ngroups) {
+                                              uint64_t* ngroups, uint32_t* longest) {
   const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= N) return;
   uint64_t m = 0;
-  uint32_t ng = 0;
+  uint32_t ng = 0, len = 0;
   for (uint32_t d = 1; d < D1; ++d) {
-    if (cnt[(uint64_t)s * D1 + d]) { m |= 1ull << d; ++ng; }
+    const uint32_t c = cnt[(uint64_t)s * D1 + d];
+    if (c) { m |= 1ull << d; ++ng; }
+    len += c;
   }
+  if (longest) atomicMax(longest, len);
   mask[s] = m;
   ngroups[s] = ng;
 }
@@ -424,6 +499,35 @@ __global__ void __launch_bounds__(kB) k_grp_off(const uint32_t* __restrict__ cnt
 // Longer groups are listed for the block sort.
 constexpr uint32_t kWaveSortMax = 1024;
 constexpr uint32_t kBlockSortMax = 16384;
+constexpr int kRowSortRegs = 16;  // words of a row per thread of k_row_sort
+// ... for rows of that many words on the average: in shorter ones most of a block
+// has no word, and a wave per group is faster (builds by group and by row, 6.4
+// 10^6 synapses in rows of 64: 2.66 and 2.85 ms; 1.3 10^7 of 128: 3.15, 3.11; 10^7
+// of 200: 2.30, 2.22)
+constexpr uint64_t kRowSortMean = 128;
+
+// Value of lane ^ j (j a power of two below 64, a constant once unrolled), by
+// moves between lanes in place of the LDS crossbar.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, 0xf, 0xf, true);
+}
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x, int j, uint32_t lane) {
+  switch (j) {
+    case 1: return dpp<0xb1>(x);              // quad_perm 1 0 3 2
+    case 2: return dpp<0x4e>(x);              // quad_perm 2 3 0 1
+    case 4: return dpp<0x1b>(dpp<0x141>(x));  // row_half_mirror (lane ^ 7), quad_perm 3 2 1 0 (lane ^ 3)
+    case 8: return dpp<0x128>(x);             // row_ror 8
+    case 16: {                                // odd rows of one copy against even rows of the other
+      const auto y = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+      return (lane & 16) ? y[0] : y[1];
+    }
+    default: {
+      const auto y = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+      return (lane & 32) ? y[0] : y[1];
+    }
+  }
+}
 
 template <int R>
 __device__ __forceinline__ void wave_sort(uint32_t* v, uint32_t lane) {
@@ -456,10 +560,10 @@ __device__ __forceinline__ void wave_sort(uint32_t* v, uint32_t lane) {
 }
 
 template <int R>
-__device__ __forceinline__ void sort_group(uint32_t* p, uint32_t L, uint32_t lane) {
+__device__ __forceinline__ void sort_group(const uint32_t* in, uint32_t* p, uint32_t L, uint32_t lane) {
   uint32_t v[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) v[r] = (64 * r + lane < L) ? p[64 * r + lane] : 0xffffffffu;
+  for (int r = 0; r < R; ++r) v[r] = (64 * r + lane < L) ? in[64 * r + lane] : 0xffffffffu;
   wave_sort<R>(v, lane);
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -484,11 +588,66 @@ __global__ void __launch_bounds__(kB) k_segsort_wave(const uint64_t* __restrict_
       continue;
     }
     const uint32_t L = (uint32_t)L64;
-    if (L <= 64) sort_group<1>(payload + b, L, lane);
-    else if (L <= 128) sort_group<2>(payload + b, L, lane);
-    else if (L <= 256) sort_group<4>(payload + b, L, lane);
-    else if (L <= 512) sort_group<8>(payload + b, L, lane);
-    else sort_group<16>(payload + b, L, lane);
+    if (L <= 64) sort_group<1>(payload + b, payload + b, L, lane);
+    else if (L <= 128) sort_group<2>(payload + b, payload + b, L, lane);
+    else if (L <= 256) sort_group<4>(payload + b, payload + b, L, lane);
+    else if (L <= 512) sort_group<8>(payload + b, payload + b, L, lane);
+    else sort_group<16>(payload + b, payload + b, L, lane);
+  }
+}
+
+// The same from the rows of k_bin_rows: a block reads a source's row, places its
+// words at their groups in LDS, and its waves sort these into the payload.  A
+// block has a thread for 16 words of a row: a launch for each block size (with the
+// largest for all, 3.0 10^8 synapses in rows of 2,100 .. 8,200 took 3.3 ms, now
+// 2.8).
+template <int kTh>
+__global__ void __launch_bounds__(kTh) k_row_sort(const uint64_t* __restrict__ off, const uint32_t* __restrict__ grp_ptr,
+                                                  uint32_t D1, const uint8_t* __restrict__ del, uint32_t* payload,
+                                                  uint32_t above, unsigned long long* longer, uint32_t* n_longer,
+                                                  uint64_t cap) {
+  constexpr int kItems = kRowSortRegs;
+  __shared__ uint32_t buf[kItems * kTh], cur[64], first[65];
+  const uint32_t s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t o = off[(uint64_t)s * D1];
+  const uint32_t len = (uint32_t)(off[(uint64_t)(s + 1) * D1] - o);
+  if (len <= above || len > (uint32_t)(kItems * kTh)) return;  // block-uniform: another launch's
+  uint32_t w[kItems], d[kItems];
+#pragma unroll
+  for (int q = 0; q < kItems; ++q) {
+    const uint32_t j = q * kTh + tid;
+    w[q] = j < len ? payload[o + j] : 0u;
+    d[q] = j < len ? del[o + j] : 0u;
+  }
+  if (tid < 64) {
+    const uint32_t x = tid < D1 ? (uint32_t)(off[(uint64_t)s * D1 + tid] - o) : len;
+    first[tid] = x;
+    cur[tid] = x;
+    if (tid == 0) first[64] = len;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kItems; ++q)
+    if (q * kTh + tid < len) buf[atomicAdd(&cur[d[q]], 1u)] = w[q];
+  __syncthreads();
+  for (uint32_t k = wv; k < D1; k += kTh / 64) {  // wave-uniform
+    const uint32_t b = first[k], L = first[k + 1] - b;
+    if (L == 0) continue;
+    uint32_t* out = payload + o + b;
+    const uint32_t* in = buf + b;
+    if (L > kWaveSortMax) {
+      for (uint32_t j = lane; j < L; j += 64) out[j] = in[j];
+      const uint32_t g = grp_ptr[s] + (uint32_t)__popcll(__ballot(lane < k && first[lane + 1] > first[lane]));
+      if (lane == 0) {
+        const uint32_t at = atomicAdd(n_longer, 1u);
+        if (at < cap) longer[at] = g;
+      }
+    } else if (L <= 64) sort_group<1>(in, out, L, lane);
+    else if (L <= 128) sort_group<2>(in, out, L, lane);
+    else if (L <= 256) sort_group<4>(in, out, L, lane);
+    else if (L <= 512) sort_group<8>(in, out, L, lane);
+    else sort_group<16>(in, out, L, lane);
   }
 }
 
@@ -638,8 +797,8 @@ hipError_t launch_scan_u64(const uint64_t* in, uint64_t n, uint64_t* out, uint64
 }
 
 hipError_t launch_masks(const uint32_t* cnt, uint32_t N, uint32_t D1, uint64_t* mask, uint64_t* ngroups,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_masks, dim3((N + kB - 1) / kB), dim3(kB), 0, s, cnt, N, D1, mask, ngroups);
+                        uint32_t* longest, hipStream_t s) {
+  hipLaunchKernelGGL(k_masks, dim3((N + kB - 1) / kB), dim3(kB), 0, s, cnt, N, D1, mask, ngroups, longest);
   return hipGetLastError();
 }
 
@@ -654,12 +813,32 @@ size_t segsort_list(uint64_t n_syn, uint64_t n_groups) {
   return (size_t)std::min<uint64_t>(n_groups, n_syn / (kWaveSortMax + 1)) + 1;
 }
 
+bool row_sort_fits(const BinBuild& bb, uint32_t D1, uint32_t longest, uint64_t mean) {
+  return bb.nbin && bb.words / D1 <= (uint32_t)kBT && longest <= 1024u * kRowSortRegs && mean >= kRowSortMean;
+}
+
+hipError_t launch_bin_rows(const BinBuild& bb, uint32_t D1, const uint64_t* off, uint32_t* payload, uint8_t* del,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_bin_rows, dim3(bb.nbin), dim3(kBT), kRowChunk * 7 + kBT * 12, s, bb, D1, off, payload, del);
+  return hipGetLastError();
+}
+
 hipError_t launch_segsort(const uint64_t* grp_off, uint64_t n_groups, uint32_t* payload, uint64_t* longer,
                           uint32_t* n_longer, uint64_t list_cap, uint64_t* big, uint32_t* nbig, uint32_t big_cap,
-                          hipStream_t s) {
+                          const RowSort& rows, hipStream_t s) {
   if (n_groups == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_segsort_wave, dim3(grid_for(n_groups, kB / 64, 1u << 20)), dim3(kB), 0, s, grp_off, n_groups,
-                     payload, (unsigned long long*)longer, n_longer, list_cap);
+  if (rows.del) {
+    uint32_t above = 0;  // a launch for each block size, over the rows that need it
+    for (uint32_t th = 256; th <= 1024 && rows.longest > above; th *= 2) {
+      auto k = th == 256 ? k_row_sort<256> : th == 512 ? k_row_sort<512> : k_row_sort<1024>;
+      hipLaunchKernelGGL(k, dim3(rows.N), dim3(th), 0, s, rows.off, rows.grp_ptr, rows.D1, rows.del, payload, above,
+                         (unsigned long long*)longer, n_longer, list_cap);
+      above = th * kRowSortRegs;
+    }
+  } else {
+    hipLaunchKernelGGL(k_segsort_wave, dim3(grid_for(n_groups, kB / 64, 1u << 20)), dim3(kB), 0, s, grp_off, n_groups,
+                       payload, (unsigned long long*)longer, n_longer, list_cap);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_segsort_block, dim3(grid_for(list_cap, 1, 1024)), dim3(kSB), kBlockSortMax * sizeof(uint32_t), s,

@@ -1623,7 +1623,7 @@ snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb
   uint16_t* d_of = dalloc<uint16_t>(net, N);
   uint64_t* d_off = dalloc<uint64_t>(net, off.size());
   uint32_t* d_cap = dalloc<uint32_t>(net, cap.size());
-  uint32_t* d_cnt = dalloc<uint32_t>(net, cap.size() + 1);
+  uint32_t* d_cnt = dalloc<uint32_t>(net, cap.size() + 2);
   uint2* d_rec = dalloc<uint2>(net, places);
   bool ok = true;
   for (void* p : {(void*)d_first, (void*)d_of, (void*)d_off, (void*)d_cap, (void*)d_cnt, (void*)d_rec}) {
@@ -1639,8 +1639,9 @@ snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb
   HIPCHK(net, copy_sync(net, d_of, of.data(), (size_t)N * 2, hipMemcpyHostToDevice));
   HIPCHK(net, copy_sync(net, d_off, off.data(), off.size() * 8, hipMemcpyHostToDevice));
   HIPCHK(net, copy_sync(net, d_cap, cap.data(), cap.size() * 4, hipMemcpyHostToDevice));
-  HIPCHK(net, hipMemsetAsync(d_cnt, 0, (cap.size() + 1) * 4, net->stream));
+  HIPCHK(net, hipMemsetAsync(d_cnt, 0, (cap.size() + 2) * 4, net->stream));
   bb.first = d_first; bb.of_src = d_of; bb.off = d_off; bb.cap = d_cap; bb.cnt = d_cnt; bb.over = d_cnt + cap.size();
+  bb.longest = bb.over + 1;
   bb.rec = d_rec;
   bb.nbin = (uint32_t)cap.size();
   return SNN_OK;
@@ -2072,9 +2073,11 @@ snn_status build_impl(snn_net* net) {
     HIPCHK(net, launch_gen_count(d_proj, (uint32_t)pd.size(), total_pairs, dmax_cfg, D1, d_cnt, s));
   }
   HIPCHK(net, launch_scan_u32(d_cnt, M, d_off, d_tmp, s));
-  HIPCHK(net, launch_masks(d_cnt, N, D1, d_mask, d_ng, s));
+  HIPCHK(net, launch_masks(d_cnt, N, D1, d_mask, d_ng, bb.nbin ? bb.longest : nullptr, s));
   HIPCHK(net, launch_scan_u64(d_ng, N, d_gp64, d_tmp, s));
   uint64_t G = 0, S = 0;
+  RowSort rows;
+  if (bb.nbin) HIPCHK(net, hipMemcpyAsync(&rows.longest, bb.longest, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(net, hipMemcpyAsync(&G, d_gp64 + N, 8, hipMemcpyDeviceToHost, s));
   HIPCHK(net, hipMemcpyAsync(&S, d_off + M, 8, hipMemcpyDeviceToHost, s));
   HIPCHK(net, hipStreamSynchronize(s));
@@ -2092,7 +2095,13 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, launch_grp_off(d_cnt, d_off, d_gp64, N, D1, d_goff, d_gp32, s));
   HIPCHK(net, hipMemcpyAsync(d_goff + G, &S, 8, hipMemcpyHostToDevice, s));
   if (bb.nbin) {
-    HIPCHK(net, launch_bin_place(bb, D1, d_off, d_pay, s));
+    uint8_t* d_del = row_sort_fits(bb, D1, rows.longest, S / N) ? dalloc<uint8_t>(net, S) : nullptr;
+    if (d_del) {
+      rows.del = d_del; rows.off = d_off; rows.grp_ptr = d_gp32; rows.D1 = D1; rows.N = N;
+      HIPCHK(net, launch_bin_rows(bb, D1, d_off, d_pay, d_del, s));
+    } else {
+      HIPCHK(net, launch_bin_place(bb, D1, d_off, d_pay, s));
+    }
     HIPCHK(net, hipStreamSynchronize(s));
     for (void* b : bin_bufs) dev_free(net, b);
   } else {
@@ -2105,10 +2114,11 @@ snn_status build_impl(snn_net* net) {
   const size_t long_cap = segsort_list(S, G);
   uint64_t* d_long; ALLOC(d_long, uint64_t, long_cap);
   HIPCHK(net, hipMemsetAsync(d_nbig, 0, 8, s));
-  HIPCHK(net, launch_segsort(d_goff, G, d_pay, d_long, d_nbig + 1, long_cap, d_big, d_nbig, big_cap, s));
+  HIPCHK(net, launch_segsort(d_goff, G, d_pay, d_long, d_nbig + 1, long_cap, d_big, d_nbig, big_cap, rows, s));
   uint32_t nbig = 0;
   HIPCHK(net, hipMemcpyAsync(&nbig, d_nbig, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(net, hipStreamSynchronize(s));
+  if (rows.del) dev_free(net, const_cast<uint8_t*>(rows.del));
   if (nbig > big_cap) return fail(net, SNN_E_UNSUPPORTED, "too many connection groups above 16384 synapses");
   if (nbig) {  // rare: very large groups are sorted on the host
     std::vector<uint64_t> big(nbig);

@@ -64,3 +64,18 @@ def test_listed_connections(snn, crowd):
     pr = dict(rule="list", src_gids=src, tgt_gids=r.integers(0, n, m), delays_ms=r.integers(1, 30, m) * 0.1,
               weights=r.choice([0.5, 1.0, -2.0], m), port=0)
     check(snn, dict(name="list", dt=0.1, seed=4, dmax=40, populations=[pop("A", n)], projections=[pr], poisson=[]))
+
+
+@pytest.mark.parametrize("length", [255, 256, 4096, 4097, 8192, 8193, 16384, 16385])
+@pytest.mark.parametrize("dmax", [1, 40])
+def test_row_lengths(snn, length, dmax):
+    """Rows of one length, at the edges of what a block sorts at once, beside
+    sources of a few synapses."""
+    ns = SYN // length + 1
+    d = ("uniform", 0.1, 0.1 * dmax) if dmax > 1 else ("const", 0.1, 0.0)
+    projs = [dict(src="S", tgt="T", rule="fixed_outdegree", K=length, weight=1.0, delay=d, port=0,
+                  weight_dist=dict(kind="uniform", low=0.0, high=1.0, levels=5)),
+             dict(src="F", tgt="T", rule="fixed_outdegree", K=2, weight=-1.0, delay=d, port=0)]
+    spec = dict(name="rows", dt=0.1, seed=6, dmax=dmax, populations=[pop("F", 3), pop("S", ns), pop("T", 3000)],
+                projections=projs, poisson=[])
+    check(snn, spec)
