@@ -28,8 +28,9 @@ def signature(spec) -> str:
 
 
 def candidates(spec) -> list:
-    """Configurations to try: direct delivery at three delivery-grid sizes,
-    binned delivery at every tile size the port count allows (at most 1024
+    """Configurations to try: the library's own choice (alone in having the
+    strips and the one-block steps of LIF networks), direct delivery by device
+    atomics at three delivery-grid sizes, binned delivery at every tile size the port count allows (at most 1024
     tiles) and, for the library's tile size, three grid sizes."""
     specs = list(spec) if isinstance(spec, (list, tuple)) else [spec]
     n = sum(W.total_neurons(sp) for sp in specs)
@@ -38,7 +39,7 @@ def candidates(spec) -> list:
     while p2 < ports:
         p2 *= 2
     tmax = 4096 // p2
-    out = [dict(delivery="direct", delivery_blocks=b) for b in (0, 128, 512)]
+    out = [dict(delivery="auto")] + [dict(delivery="direct", delivery_blocks=b) for b in (0, 128, 512)]
     t = 256
     while t <= tmax:
         if (n + t - 1) // t <= 1024:
