@@ -1852,6 +1852,11 @@ snn_status build_impl(snn_net* net) {
     memset(&d, 0, sizeof d);
     d.src_first = pr.src_first; d.src_n = pr.src_n; d.tgt_first = pr.tgt_first; d.tgt_n = pr.tgt_n;
     d.rule = (uint32_t)pr.rule;
+    d.tpop = 0;
+    if (pr.rule != kRuleList && pr.tgt_n) {
+      const uint32_t k = pop_of(net, pr.tgt_first);
+      if (pr.tgt_first + pr.tgt_n <= net->pops[k].first + net->pops[k].n) d.tpop = k + 1;
+    }
     const bool single = pr.rule == SNN_RULE_ONE_TO_ONE || pr.rule == SNN_RULE_FIXED_TOTAL_NUMBER || pr.rule == kRuleList;
     d.K = pr.K; d.kpairs = single ? 1u : (pr.K + 1) / 2; d.index = pr.local;
     d.gid_base = net->insts[pr.inst].first_gid; d.seed = net->insts[pr.inst].seed;

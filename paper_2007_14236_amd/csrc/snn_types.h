@@ -113,7 +113,7 @@ struct ProjDev {
   uint32_t kpairs;         // work items per entity: ceil(K / 2) (1 for one-to-one and fixed total)
   uint32_t index;          // creation index within its instance (Philox counter word 1, bits 40+)
   uint32_t gid_base;       // first gid of its instance (counters use instance-local gids)
-  uint32_t rule, pad;
+  uint32_t rule, tpop;     // tpop: 1 + the population that holds all its targets (0: several)
   uint64_t seed;           // generator key of its instance
   uint64_t pair_begin;     // prefix of entities * kpairs over projections
   const uint32_t* lsrc;    // user-defined list: source, target and delay (steps) of synapse j
