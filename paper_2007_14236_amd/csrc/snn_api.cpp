@@ -279,6 +279,7 @@ struct snn_net {
   size_t pinned_words = 0;
   uint32_t tile_neurons = 0;       // binned delivery (0: direct)
   size_t small_ring_bytes = 0;
+  bool lean = false;               // build without the arrays that only make it or the steps faster
   uint64_t acc_step = ~0ull;       // pulled delivery: the step whose input a restore left in acc
 
   // host raster
@@ -1313,7 +1314,14 @@ snn_status snn_build(snn_net* net) {
   if (net->built) return fail(net, SNN_E_STATE, "already built");
   if (net->released) return fail(net, SNN_E_STATE, "released networks are not built again");
   if (net->N == 0) return fail(net, SNN_E_INVALID, "empty network");
-  const snn_status st = build_impl(net);
+  snn_status st = build_impl(net);
+  if (st == SNN_E_NOMEM) {
+    // what is built only for speed may have taken the memory that the rest needs
+    release_build(net);
+    net->lean = true;
+    st = build_impl(net);
+    net->lean = false;
+  }
   if (st != SNN_OK) {
     const std::string msg = net->err;
     release_build(net);
@@ -1389,7 +1397,7 @@ uint32_t class_slots(const snn_net* net, const std::vector<std::vector<uint32_t>
 snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
   NetDev& nd = net->nd;
   hipStream_t s = net->stream;
-  if (nd.N > kSmallN || nd.P > 2 || nd.npop > kSmallPops || nd.n_syn > kSmallSyn || net->nch) return SNN_OK;
+  if (net->lean || nd.N > kSmallN || nd.P > 2 || nd.npop > kSmallPops || nd.n_syn > kSmallSyn || net->nch) return SNN_OK;
   std::vector<uint8_t> slot;
   std::vector<PullPop> pp;
   NetDev x = nd;
@@ -1436,7 +1444,7 @@ snn_status build_strips(snn_net* net) {
   x.strip_n = std::min<uint32_t>(kStripN, std::max<uint32_t>(64, ((nd.N + kStripGrid - 1) / kStripGrid + 63) / 64 * 64));
   const uint64_t S = (nd.N + x.strip_n - 1) / x.strip_n;
   const uint64_t rows = (uint64_t)nd.N * (S + 1), spill = (uint64_t)nd.R * nd.N * nd.P;
-  if (S > kStripMax || !nd.n_syn || nd.n_syn >> 32 || nd.npop > kStripPops || nd.npois > kStripPois) return SNN_OK;
+  if (net->lean || S > kStripMax || !nd.n_syn || nd.n_syn >> 32 || nd.npop > kStripPops || nd.npois > kStripPois) return SNN_OK;
   if (rows * 4 > std::max<uint64_t>(kStripFree, nd.n_syn * 4) || spill * 8 > std::max<uint64_t>(kStripFree, nd.n_syn * 4))
     return SNN_OK;
   x.n_strips = (uint32_t)S;
@@ -1584,7 +1592,7 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
 // do not fit the bins' counters, and where the scratch (8 bytes a synapse) is
 // too large or cannot be had; bufs: what was allocated.
 snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb, std::vector<void*>& bufs) {
-  if (total_syn < kBinBuildMin || total_syn > kBinBuildMax64) return SNN_OK;
+  if (net->lean || total_syn < kBinBuildMin || total_syn > kBinBuildMax64) return SNN_OK;
   const uint32_t N = net->N;
   std::map<uint32_t, double> step;  // expected synapses per source, its changes along the gids
   for (const HostProj& pr : net->projs) {
@@ -2403,7 +2411,7 @@ snn_status build_impl(snn_net* net) {
         dev_free(net, d_rc); dev_free(net, d_tl); dev_free(net, d_rt);
         const bool runs = !too_long && total && nd.n_syn >= kRunMinMean * total;
         // the targets pull their input (kernels_pull.hip) unless a bin size was asked for
-        if (runs && !net->cfg.bin_capacity) {
+        if (runs && !net->cfg.bin_capacity && !net->lean) {
           if ((st = build_pull(net, pop_cls))) return st;
         }
         if (nd.n_pull) {
