@@ -61,10 +61,15 @@ BYTES_PER_PAIR = 28
 BYTES_PER_SPIKE = 28
 
 
-def measured_traffic(workload: str, kernel: str, tile_neurons: int = 0):
-    """HBM bytes per launch of the step kernel from the committed counter
-    summary, or None when the kernel sources have changed since it was taken
-    (or it was taken for another kernel or tile size on this workload)."""
+# The record's "kernel" of a step: the way of delivery, and in "runs" what runs it
+DELIVERY_OF = {"k_step_strip": "k_step", "k_small": "k_step", "k_pull": "k_step_binned_runs"}
+
+
+def measured_traffic(workload: str, kernel: str, tile_neurons: int = 0, runs: str | None = None):
+    """HBM bytes per launch of the step kernel (per step, where two kernels run
+    it) from the committed counter summary, or None when the kernel sources have
+    changed since it was taken (or it was taken for another kernel or tile size
+    on this workload)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
@@ -78,6 +83,8 @@ def measured_traffic(workload: str, kernel: str, tile_neurons: int = 0):
         return None
     ent = rec["workloads"][workload]
     if ent["kernel"] != kernel or ent.get("tile_neurons", tile_neurons) != tile_neurons:
+        return None
+    if ent.get("runs", kernel) != (runs or kernel):
         return None
     return ent["bytes_per_launch"]
 
@@ -137,7 +144,7 @@ def step_roofline(net, specs: list, mode: str, steps: int, c0: dict, c1: dict, p
         "kernel": kernel, "bound": "hbm",
         "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
         "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 5),
-        "traffic": measured_traffic(workload, kernel, c2["tile_neurons"]),
+        "traffic": measured_traffic(workload, DELIVERY_OF.get(kernel, kernel), c2["tile_neurons"], kernel),
         "avg_launch_us": round(dev_ms * 1e3, 3), "bytes_per_launch": round(dlv_bytes),
         "timing": "HIP events on the library stream around the timed call's graph launches, per step",
         "isolated_launch_us": round(iso_ms * 1e3, 3),
