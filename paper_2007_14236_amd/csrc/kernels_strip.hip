@@ -19,7 +19,7 @@
 // behind them.  Per step, with device atomics and so: that network at 126,000
 // events 13.8 -> 9.3 us; LIF networks with delta PSCs of 2,100 neurons and 1,900
 // events 7.9 -> 6.1 us, 10,000 and 45,000 10.0 -> 7.1, 150,000 and 680,000 46.9
-// -> 24.7, 450,000 and 2.0 10^6 143 -> 64.
+// -> 24.7, 450,000 and 2.0 10^6 143 -> 54.
 //
 // The spike books and, once folded, input and counters are those of the other
 // step kernels, so readback and snapshots are the same.
@@ -214,8 +214,9 @@ struct TableWords {
 };
 constexpr uint32_t kPopWords = sizeof(PopDev) / 4;
 
-template <int P>
-__global__ void __launch_bounds__(kT) k_step_strip(StripNet nd, uint32_t rel) {
+// kWaves8: eight waves a SIMD, so that a CU holds two blocks.
+template <int P, bool kWaves8>
+__global__ void __launch_bounds__(kT, kWaves8 ? 8 : 4) k_step_strip(StripNet nd, uint32_t rel) {
   extern __shared__ __align__(16) char lds[];
   StripHead& h = *reinterpret_cast<StripHead*>(lds);
   int64_t* acc = strip_acc(lds);
@@ -593,7 +594,13 @@ size_t strip_lds(const NetDev& nd) { return sizeof(StripHead) + (size_t)nd.strip
 }  // namespace
 
 hipError_t launch_strip_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
-  auto k = nd.P == 1 ? k_step_strip<1> : nd.P == 2 ? k_step_strip<2> : k_step_strip<kMaxPorts>;
+  // with fewer scalar registers (they hold the network's pointers) a block takes
+  // 0.8 us longer, which pays where there are more blocks than CUs: 5,000 neurons
+  // in 79 strips 6.7 and 7.7 us a step, 300,000 in 293 48.6 and 43.0, 450,000 in
+  // 440 64.1 and 54.5
+  auto k = nd.n_strips <= 256
+               ? (nd.P == 1 ? k_step_strip<1, false> : nd.P == 2 ? k_step_strip<2, false> : k_step_strip<kMaxPorts, false>)
+               : (nd.P == 1 ? k_step_strip<1, true> : nd.P == 2 ? k_step_strip<2, true> : k_step_strip<kMaxPorts, true>);
   if (start) hipExtLaunchKernelGGL(k, dim3(nd.n_strips), dim3(kT), strip_lds(nd), s, start, stop, 0, strip_net(nd), rel);
   else hipLaunchKernelGGL(k, dim3(nd.n_strips), dim3(kT), strip_lds(nd), s, strip_net(nd), rel);
   return hipGetLastError();

@@ -135,6 +135,24 @@ def test_strips_bit_exact(snn, name):
         assert np.array_equal(g.get_state(var, port=port), d.get_state(var, port=port))
 
 
+@pytest.mark.parametrize("ports_", [1, 2])
+def test_more_strips_than_compute_units(snn, ports_):
+    """Two strips on a compute unit: 263,000 neurons, against device atomics."""
+    sp = brunel(263_000, 265) if ports_ == 1 else ports(2, n=200_000)
+    if ports_ == 2:
+        for p in sp["projections"]:
+            p["K"] = 70
+    g, d = snn.Net(sp), snn.Net(sp, delivery="direct")
+    for x in (g, d):
+        x.simulate(61)
+    for x, y in zip(g.spikes(), d.spikes()):
+        assert len(x) > 0 and np.array_equal(x, y)
+    assert np.array_equal(g.get_input(ports_ - 1), d.get_input(ports_ - 1))
+    assert np.array_equal(g.get_state("V_m"), d.get_state("V_m"))
+    cg, cd = g.counters(), d.counters()
+    assert all(cg[k] == cd[k] for k in ("spikes", "events", "pairs"))
+
+
 @pytest.mark.parametrize("name", ["delays_1_2", "63_delays", "devices", "instances"])
 @pytest.mark.parametrize("src,dst", [("auto", "auto"), ("auto", "direct"), ("direct", "auto")])
 def test_strip_snapshots(snn, name, src, dst):
