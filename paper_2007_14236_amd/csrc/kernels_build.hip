@@ -219,12 +219,15 @@ __global__ void __launch_bounds__(kB) k_gen(const ProjDev* __restrict__ projs, u
 
 // ---- drawn once, through bins of consecutive sources ----
 constexpr int kBT = 1024;     // threads of the three kernels
-constexpr int kBinItems = 8;  // work items of a thread of k_bin_gen: up to 16 synapses
+// Work items of a thread of k_bin_gen, up to 2 synapses each: as many as stay in
+// registers at eight waves a SIMD (two blocks on a CU).  8 items with one block
+// 4.5 ms for 3.0 10^8 synapses, with two 3.85 (in scratch memory), 4 items 3.1.
+constexpr int kBinItems = 4;
 
 // Block = kBT * kBinItems work items.  Their synapses stay in registers while
 // they are counted per bin in LDS; one device atomic per touched bin reserves
 // its place, then each synapse is written.  A bin that is full sets *over.
-__global__ void __launch_bounds__(kBT) k_bin_gen(const ProjDev* __restrict__ projs, uint32_t nproj,
+__global__ void __launch_bounds__(kBT, 8) k_bin_gen(const ProjDev* __restrict__ projs, uint32_t nproj,
                                                  uint64_t total_pairs, uint32_t dmax_cfg, const uint16_t* cls_of,
                                                  const ProjW* pw, const uint32_t* pop_first, uint32_t npop,
                                                  uint32_t cls_bits, BinBuild bb) {
