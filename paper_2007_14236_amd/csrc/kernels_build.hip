@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(kB) k_gen(const ProjDev* __restrict__ projs, u
 constexpr int kBT = 1024;     // threads of the three kernels
 // Work items of a thread of k_bin_gen, up to 2 synapses each: as many as stay in
 // registers at eight waves a SIMD (two blocks on a CU).  8 items with one block
-// 4.5 ms for 3.0 10^8 synapses, with two 3.85 (in scratch memory), 4 items 3.1.
+// 4.5 ms for 3.0 10^8 synapses, with two 3.85 (in scratch memory), 4 items 3.2.
 constexpr int kBinItems = 4;
 
 // Block = kBT * kBinItems work items.  Their synapses stay in registers while
