@@ -38,8 +38,6 @@ hipError_t launch_grp_off(const uint32_t* cnt, const uint64_t* off, const uint64
 // into: sources [first[b], first[b + 1]), places off[b] .. off[b] + cap[b] of
 // rec (source in the bin << 6 | delay, payload), cnt[b] taken; *over is set when
 // one was full.  words: most (source, delay) counters of a bin.
-constexpr uint32_t kBinBuildMax = 4096;   // bins
-constexpr uint32_t kBinBuildWords = 24576;
 struct BinBuild {
   uint32_t nbin, words;
   const uint32_t* first;    // [nbin + 1]

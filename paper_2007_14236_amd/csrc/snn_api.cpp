@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "../../include/snn.h"
+#include "bin_plan.h"
 #include "kernels.h"
 #include "snn_types.h"
 
@@ -1586,9 +1587,8 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
   return SNN_OK;
 }
 
-// Bins of consecutive sources for the build (kernels_build.hip), of about equal
-// numbers of synapses as the rules expect them, each with room for eight
-// standard deviations more.  bb.nbin stays 0 for small networks, sources that
+// Bins of consecutive sources for the build (kernels_build.hip), planned by the
+// numbers of synapses that the rules expect.  bb.nbin stays 0 for small networks, sources that
 // do not fit the bins' counters, and where the scratch (8 bytes a synapse) is
 // too large or cannot be had; bufs: what was allocated.
 snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb, std::vector<void*>& bufs) {
@@ -1601,30 +1601,11 @@ snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb
     step[pr.src_first] += per;
     step[pr.src_first + pr.src_n] -= per;
   }
-  const uint32_t most = kBinBuildWords / D1;  // sources of a bin, at most
-  const double want = std::max((double)total_syn / 1000.0, 8192.0);
-  std::vector<uint32_t> first{0}, cap;
-  std::vector<uint64_t> off;
-  std::vector<uint16_t> of(N);
-  uint64_t places = 0;
-  double rate = 0.0, in_bin = 0.0;
-  auto close = [&](uint32_t end) {
-    const uint64_t c = (uint64_t)(in_bin + 8.0 * std::sqrt(in_bin) + 256.0);
-    off.push_back(places);
-    cap.push_back((uint32_t)std::min<uint64_t>(c, 0x7fffffffu));
-    places += c;
-    first.push_back(end);
-    in_bin = 0.0;
-  };
-  auto next = step.begin();
-  for (uint32_t i = 0; i < N; ++i) {
-    while (next != step.end() && next->first <= i) { rate += next->second; ++next; }
-    if (i > first.back() && (i - first.back() >= most || in_bin + 0.5 * rate > want)) close(i);
-    if (cap.size() >= kBinBuildMax) return SNN_OK;
-    of[i] = (uint16_t)cap.size();
-    in_bin += rate;
-  }
-  close(N);
+  BinPlan plan;
+  if (!plan_source_bins(N, total_syn, D1, step, plan)) return SNN_OK;
+  const std::vector<uint32_t>&first = plan.first, &cap = plan.cap;
+  const std::vector<uint64_t>& off = plan.off;
+  const std::vector<uint16_t>& of = plan.of;
   bb.nbin = 0;
   for (size_t b = 0; b < cap.size(); ++b) bb.words = std::max(bb.words, (first[b + 1] - first[b]) * D1);
   uint32_t* d_first = dalloc<uint32_t>(net, first.size());
@@ -1632,7 +1613,7 @@ snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb
   uint64_t* d_off = dalloc<uint64_t>(net, off.size());
   uint32_t* d_cap = dalloc<uint32_t>(net, cap.size());
   uint32_t* d_cnt = dalloc<uint32_t>(net, cap.size() + 2);
-  uint2* d_rec = dalloc<uint2>(net, places);
+  uint2* d_rec = dalloc<uint2>(net, plan.places);
   bool ok = true;
   for (void* p : {(void*)d_first, (void*)d_of, (void*)d_off, (void*)d_cap, (void*)d_cnt, (void*)d_rec}) {
     if (p) bufs.push_back(p);

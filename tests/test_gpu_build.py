@@ -79,3 +79,12 @@ def test_row_lengths(snn, length, dmax):
     spec = dict(name="rows", dt=0.1, seed=6, dmax=dmax, populations=[pop("F", 3), pop("S", ns), pop("T", 3000)],
                 projections=projs, poisson=[])
     check(snn, spec)
+
+
+@pytest.mark.parametrize("na,ka,nb,kb", [(1295, 146, 927, 270), (508, 198, 2324, 168)])
+def test_targets_behind_two_kinds_of_sources(snn, na, ka, nb, kb):
+    """6,000 neurons without synapses of their own behind populations whose
+    expected out-degrees do not cancel exactly: bins of such neurons alone."""
+    projs = [dict(src=s, tgt="T", K=k, weight=1.0, delay=("uniform", 0.1, 6.4), port=0) for s, k in (("A", ka), ("B", kb))]
+    check(snn, dict(name="behind", dt=0.1, seed=4, dmax=63, populations=[pop("A", na), pop("B", nb), pop("T", 6000)],
+                    projections=projs, poisson=[]))
