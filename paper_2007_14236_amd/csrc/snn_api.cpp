@@ -338,6 +338,10 @@ void* dev_alloc(snn_net* net, size_t bytes) {
   if (p) {
     net->allocs.push_back({p, bytes});
     net->dev_bytes += bytes;
+  } else {
+    // a failed hipMalloc, here or in the caller's allocator, stays this thread's
+    // last error: left there, the next launch would be taken to have failed
+    (void)hipGetLastError();
   }
   return p;
 }

@@ -1,0 +1,90 @@
+"""Builds, restores and served requests when device memory runs out: what is
+allocated only for speed may be refused at any point, by allocators that leave
+HIP's error behind as a failed hipMalloc does, and a restore asks for none."""
+import ctypes as C
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2007_14236_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _name(request):
+    print(f"\n[gpu-case] {request.node.nodeid}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def snn():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2007_14236_amd import snn as S
+    S.lib()
+    return S
+
+
+def brunel(n, k, seed=3, delay=("uniform", 0.1, 1.4), dmax=25):
+    return W.brunel_lif(n=n, k=k, seed=seed, delay=delay, dmax=dmax, nu_ext=260.0)
+
+
+def budget_allocator(snn, limit):
+    """At most `limit` bytes; what is beyond is refused after a hipMalloc that fails."""
+    hip_malloc = snn.lib().hipMalloc
+    hip_malloc.restype, hip_malloc.argtypes = C.c_int, [C.POINTER(C.c_void_p), C.c_size_t]
+
+    class Budget(snn.TorchAllocator):
+        def __init__(self):
+            super().__init__()
+            self.limit, self.held, self.peak, self.sizes = limit, 0, 0, {}
+
+        def _a(self, nbytes, user):
+            if self.held + nbytes > self.limit:
+                assert hip_malloc(C.byref(C.c_void_p()), 1 << 60) != 0
+                return None
+            p = super()._a(nbytes, user)
+            if p:
+                self.sizes[p] = nbytes
+                self.held += nbytes
+                self.peak = max(self.peak, self.held)
+            return p
+
+        def _f(self, ptr, user):
+            self.held -= self.sizes.pop(ptr, 0)
+            super()._f(ptr, user)
+
+    return Budget()
+
+
+NETS = {
+    "strips": (lambda: [brunel(2100, 600)], dict(delivery="auto"), dict(delivery="direct")),
+    "small": (lambda: [brunel(1500, 100)], dict(delivery="auto"), dict(delivery="direct")),
+    "pull": (lambda: [brunel(5000, 300), brunel(700, 300, seed=4)], dict(delivery="binned"),
+             dict(delivery="binned", bin_capacity=1 << 30)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(NETS))
+def test_a_refusal_that_leaves_an_error_behind(snn, name):
+    """Budgets from what the plain network needs to what it takes with all that
+    makes it faster: each builds, and gives the same raster."""
+    make, kw, plain_kw = NETS[name]
+
+    def run(limit, kw):
+        al = budget_allocator(snn, limit)
+        net = snn.Net(make(), allocator=al, **kw)
+        net.simulate(60)
+        sp, peak = net.spikes(), al.peak
+        net.close()
+        return sp, peak
+
+    ref, plain = run(1 << 40, plain_kw)
+    _, full = run(1 << 40, kw)
+    assert len(ref[0]) > 0
+    for limit in np.linspace(plain, full, 9).astype(np.int64):
+        sp, _ = run(int(limit), kw)
+        assert all(np.array_equal(a, b) for a, b in zip(ref, sp)), limit
