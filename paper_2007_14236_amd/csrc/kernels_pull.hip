@@ -477,7 +477,11 @@ hipError_t launch_pull_pay(const NetDev& nd, const PullInst& pi, uint64_t syn, u
   return hipGetLastError();
 }
 
-hipError_t launch_pull_restore(const NetDev& nd, uint32_t buf, SpikeRec* tmp, hipStream_t s) {
+// The records of a slot are put by in the counts, which the next step does not
+// read (its input lies in acc) and then writes.
+static_assert(kPullParts * sizeof(uint32_t) >= sizeof(SpikeRec), "N records fit the counts");
+hipError_t launch_pull_restore(const NetDev& nd, uint32_t buf, hipStream_t s) {
+  SpikeRec* tmp = reinterpret_cast<SpikeRec*>(nd.pull_cnt);
   hipLaunchKernelGGL(k_pull_take_bins, dim3(nd.n_tiles), dim3(kB), 0, s, nd, buf);
   for (uint32_t slot = 0; slot < nd.R; ++slot) {
     const hipError_t e = hipMemcpyAsync(tmp, nd.recent + (size_t)slot * nd.N, (size_t)nd.N * sizeof(SpikeRec),

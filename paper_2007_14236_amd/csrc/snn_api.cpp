@@ -1101,12 +1101,8 @@ snn_status snn_restore(snn_net* net, const void* buf, size_t size) {
     HIPCHK(net, hipStreamSynchronize(net->stream));
   }
   if (net->nd.n_pull) {  // the next step takes its input from acc
-    SpikeRec* tmp = dalloc<SpikeRec>(net, net->nd.N);
-    if (!tmp) return fail(net, SNN_E_NOMEM, "allocation failed");
-    hipError_t e = launch_pull_restore(net->nd, (uint32_t)(h.cur_step % kInBuf), tmp, net->stream);
-    if (e == hipSuccess) e = copy_sync(net, net->nd.pull_acc_step, &h.cur_step, 8, hipMemcpyHostToDevice);
-    dev_free(net, tmp);
-    if (e != hipSuccess) return fail(net, SNN_E_DEVICE, "restore: %s", hipGetErrorString(e));
+    HIPCHK(net, launch_pull_restore(net->nd, (uint32_t)(h.cur_step % kInBuf), net->stream));
+    HIPCHK(net, copy_sync(net, net->nd.pull_acc_step, &h.cur_step, 8, hipMemcpyHostToDevice));
     net->acc_step = h.cur_step;
   }
   net->cur_step = net->drained_step = h.cur_step;

@@ -88,3 +88,21 @@ def test_a_refusal_that_leaves_an_error_behind(snn, name):
     for limit in np.linspace(plain, full, 9).astype(np.int64):
         sp, _ = run(int(limit), kw)
         assert all(np.array_equal(a, b) for a, b in zip(ref, sp)), limit
+
+
+def test_restore_allocates_nothing(snn):
+    """A pulled network whose allocator gives nothing after the build."""
+    al = budget_allocator(snn, 1 << 40)
+    make, kw, _ = NETS["pull"]
+    a, b = snn.Net(make(), **kw), snn.Net(make(), allocator=al, **kw)
+    a.simulate(47)
+    b.simulate(30)
+    snap = a.snapshot()
+    al.limit = al.held
+    b.restore(snap)
+    for x in (a, b):
+        x.simulate(40)
+    for x, y in zip(a.spikes(47, 87), b.spikes(47, 87)):
+        assert len(x) > 0 and np.array_equal(x, y)
+    assert np.array_equal(a.get_state("V_m"), b.get_state("V_m"))
+    assert all(a.counters()[k] == b.counters()[k] for k in ("steps", "spikes", "events", "pairs"))
