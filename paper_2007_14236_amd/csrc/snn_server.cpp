@@ -70,7 +70,8 @@ struct Job {
   std::string err;
   size_t bytes = 0, bytes_peak = 0;  // device bytes held now, and at most
   size_t need = 0;                   // known need: bytes held when an allocation was refused, plus that allocation
-  bool refused = false;
+  bool refused = false;              // the last allocation that failed was refused by the budget: it ends a build
+                                     // (what a build can do without may have been refused before)
   int attempts = 0;
   std::unordered_map<void*, size_t> sizes;
   double t_submit = 0, t_start = 0, t_done = 0;
@@ -102,6 +103,7 @@ void* srv_alloc(size_t bytes, void* user) {
   if (!p) {
     s->in_use -= bytes;
     j->bytes -= bytes;
+    j->refused = false;  // the device's failure, not the budget's
   } else {
     j->sizes[p] = bytes;
   }

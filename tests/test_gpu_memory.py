@@ -106,3 +106,42 @@ def test_restore_allocates_nothing(snn):
         assert len(x) > 0 and np.array_equal(x, y)
     assert np.array_equal(a.get_state("V_m"), b.get_state("V_m"))
     assert all(a.counters()[k] == b.counters()[k] for k in ("steps", "spikes", "events", "pairs"))
+
+
+class Server:
+    """The library's request server, one request at a time."""
+
+    def __init__(self, snn, budget, slots):
+        self.S, self.L, self.h = snn, snn.lib(), C.c_void_p()
+        assert self.L.snn_server_create(int(budget), slots, C.byref(self.h)) == 0
+
+    def submit(self, net, steps):
+        t = C.c_uint64()
+        assert self.L.snn_server_submit(self.h, net.h, steps, C.byref(t)) == 0
+        return t.value
+
+    def result(self, ticket, timeout=60.0):
+        out, info = C.c_void_p(), self.S.JobInfo()
+        assert self.L.snn_server_wait(self.h, ticket, timeout) == 0
+        self.L.snn_server_result(self.h, ticket, C.byref(out), C.byref(info))
+        return info
+
+    def close(self):
+        self.L.snn_server_destroy(self.h)
+
+
+def test_served_network_without_device_memory_fails_as_such(snn):
+    """The budget refuses the bins' scratch (12 10^6 synapses), then the device
+    has no room for the raster ring (32 MiB): that is the failure, once."""
+    class NoRing(snn.TorchAllocator):
+        def _a(self, nbytes, user):
+            return None if nbytes == 32 << 20 else super()._a(nbytes, user)
+
+    net = snn.Net(brunel(4000, 3000), allocator=NoRing(), build=False)
+    srv = Server(snn, 120 << 20, 1)
+    try:
+        info = srv.result(srv.submit(net, 20))
+        assert info.status == -2 and info.attempts == 1, (info.status, info.attempts, info.error)
+    finally:
+        srv.close()
+        net.close()
