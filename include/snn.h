@@ -470,7 +470,8 @@ snn_status snn_get_weights(snn_net* net, int64_t* wq, size_t* n_syn);
    (snn_release), so requests submitted while others run are admitted as
    slots and memory free up and their work overlaps on the device.  Every
    device allocation of a served network passes through the server, which
-   refuses one that would exceed the budget: the build fails and releases
+   refuses one that would exceed the budget (what a network can do without,
+   to build or step faster, only within budget / slots): the build fails and releases
    what it had allocated, and the request goes back to the head of the queue
    with that amount as its known need.  A request whose known need exceeds
    the budget, or that cannot fit with nothing else on the device, fails

@@ -281,6 +281,7 @@ struct snn_net {
   uint32_t tile_neurons = 0;       // binned delivery (0: direct)
   size_t small_ring_bytes = 0;
   bool lean = false;               // build without the arrays that only make it or the steps faster
+  bool extra = false;              // such an array is being allocated
   uint64_t acc_step = ~0ull;       // pulled delivery: the step whose input a restore left in acc
 
   // host raster
@@ -363,6 +364,13 @@ template <typename T>
 T* dalloc(snn_net* net, size_t count) {
   return static_cast<T*>(dev_alloc(net, count * sizeof(T)));
 }
+
+// While it lives, what is allocated only makes the build or the steps faster.
+struct ExtraMemory {
+  snn_net* net;
+  explicit ExtraMemory(snn_net* n) : net(n) { net->extra = true; }
+  ~ExtraMemory() { net->extra = false; }
+};
 
 int pop_of(const snn_net* net, uint32_t gid) {
   for (size_t k = 0; k < net->pops.size(); ++k)
@@ -1396,6 +1404,7 @@ uint32_t class_slots(const snn_net* net, const std::vector<std::vector<uint32_t>
 // 16,800 events 6.8 us; by a launch per step 8.1 and 9.0 us; at a rate of a
 // spike per neuron and 2 ms, 2^19 synapses are 26,000 events a step).
 snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
+  const ExtraMemory extra(net);
   NetDev& nd = net->nd;
   hipStream_t s = net->stream;
   if (net->lean || nd.N > kSmallN || nd.P > 2 || nd.npop > kSmallPops || nd.n_syn > kSmallSyn || net->nch) return SNN_OK;
@@ -1439,6 +1448,7 @@ snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& p
 // LDS.  A list holds a quarter of the events that a volley of the whole network
 // brings; what lies beyond goes to the spill.
 snn_status build_strips(snn_net* net) {
+  const ExtraMemory extra(net);
   const NetDev& nd = net->nd;
   NetDev x = nd;
   hipStream_t s = net->stream;
@@ -1482,6 +1492,7 @@ snn_status build_strips(snn_net* net) {
 // counts (class_slots), runs too short, more tiles or populations of a slice
 // than the kernels hold, or no memory for it.
 snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
+  const ExtraMemory extra(net);
   NetDev& nd = net->nd;
   hipStream_t s = net->stream;
   const uint32_t npop = nd.npop, ncls = nd.n_classes;
@@ -1592,6 +1603,7 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
 // do not fit the bins' counters, and where the scratch (8 bytes a synapse) is
 // too large or cannot be had; bufs: what was allocated.
 snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb, std::vector<void*>& bufs) {
+  const ExtraMemory extra(net);
   if (net->lean || total_syn < kBinBuildMin || total_syn > kBinBuildMax64) return SNN_OK;
   const uint32_t N = net->N;
   std::map<uint32_t, double> step;  // expected synapses per source, its changes along the gids
@@ -2089,7 +2101,11 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, launch_grp_off(d_cnt, d_off, d_gp64, N, D1, d_goff, d_gp32, s));
   HIPCHK(net, hipMemcpyAsync(d_goff + G, &S, 8, hipMemcpyHostToDevice, s));
   if (bb.nbin) {
-    uint8_t* d_del = row_sort_fits(bb, D1, rows.longest, S / N) ? dalloc<uint8_t>(net, S) : nullptr;
+    uint8_t* d_del = nullptr;
+    if (row_sort_fits(bb, D1, rows.longest, S / N)) {
+      const ExtraMemory extra(net);
+      d_del = dalloc<uint8_t>(net, S);
+    }
     if (d_del) {
       rows.del = d_del; rows.off = d_off; rows.grp_ptr = d_gp32; rows.D1 = D1; rows.N = N;
       HIPCHK(net, launch_bin_rows(bb, D1, d_off, d_pay, d_del, s));
@@ -2269,6 +2285,7 @@ snn_status build_impl(snn_net* net) {
   }
 
   // ---- delivery mode: direct atomics or bins per target tile ----
+  uint64_t *d_runs = nullptr, n_runs = 0;  // binned: prefix of the groups' tile runs, where these are long
   {
     uint32_t P2 = 1;
     while (P2 < P) P2 <<= 1;
@@ -2375,44 +2392,26 @@ snn_status build_impl(snn_net* net) {
       // tile runs: the synapses of a group onto one tile are contiguous (groups
       // are sorted by target); where they are long on average, the count pass of
       // the binned flush reads one descriptor per run instead of every synapse
-      const uint64_t G = nd.n_groups;
       if (!nd.n_rules && !net->has_adex && nd.tile_win && G) {
         uint32_t* d_rc; ALLOC(d_rc, uint32_t, G);
         uint32_t* d_tl; ALLOC(d_tl, uint32_t, 1);
-        uint64_t* d_gr; ALLOC(d_gr, uint64_t, G + 1);
+        ALLOC(d_runs, uint64_t, G + 1);
         uint64_t* d_rt; ALLOC(d_rt, uint64_t, scan_tmp_words(G));
         HIPCHK(net, hipMemsetAsync(d_tl, 0, 4, s));
         HIPCHK(net, launch_runs(false, nd.grp_off, G, nd.payload, nd.cls_bits, tsh, d_rc, nullptr, nullptr, d_tl, s));
-        HIPCHK(net, launch_scan_u32(d_rc, G, d_gr, d_rt, s));
-        uint64_t total = 0;
+        HIPCHK(net, launch_scan_u32(d_rc, G, d_runs, d_rt, s));
         uint32_t too_long = 0;
-        HIPCHK(net, hipMemcpyAsync(&total, d_gr + G, 8, hipMemcpyDeviceToHost, s));
+        HIPCHK(net, hipMemcpyAsync(&n_runs, d_runs + G, 8, hipMemcpyDeviceToHost, s));
         HIPCHK(net, hipMemcpyAsync(&too_long, d_tl, 4, hipMemcpyDeviceToHost, s));
         HIPCHK(net, hipStreamSynchronize(s));
         dev_free(net, d_rc); dev_free(net, d_tl); dev_free(net, d_rt);
-        const bool runs = !too_long && total && nd.n_syn >= kRunMinMean * total;
-        // the targets pull their input (kernels_pull.hip) unless a bin size was asked for
-        if (runs && !net->cfg.bin_capacity && !net->lean) {
-          if ((st = build_pull(net, pop_cls))) return st;
-        }
-        if (nd.n_pull) {
-          dev_free(net, d_gr);
-          nd.tile_runs = 1;
-        } else if (runs) {
-          uint32_t* d_rd; ALLOC(d_rd, uint32_t, total);
-          HIPCHK(net, launch_runs(true, nd.grp_off, G, nd.payload, nd.cls_bits, tsh, nullptr, d_gr, d_rd, nullptr, s));
-          nd.grp_run = d_gr; nd.run_desc = d_rd; nd.tile_runs = 1;
-        } else {
-          dev_free(net, d_gr);
+        if (too_long || !n_runs || nd.n_syn < kRunMinMean * n_runs) {
+          dev_free(net, d_runs);
+          d_runs = nullptr;
         }
       }
     }
   }
-
-  net->unit_shift = nd.n_tiles ? nd.tile_shift : 6u;
-  if (!nd.n_tiles && !net->has_adex && !nd.n_rules && !(net->cfg.flags & SNN_F_DELIVERY_DIRECT) &&
-      ((st = build_small(net, pop_cls)) || (!nd.small_row && (st = build_strips(net)))))
-    return st;
 
   // ---- spike buffers ----
   net->drain_steps = std::max<uint64_t>(kGraphSteps, std::min<uint64_t>(1000, ((1ull << 25) / N) / kGraphSteps * kGraphSteps));
@@ -2445,7 +2444,6 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, hipMemsetAsync(nd.blk_stats, 0, (size_t)kBlkStats * nd.nblk_upd * 8, s));
   ALLOC(nd.ctrl, Ctrl, 1);
   HIPCHK(net, hipMemsetAsync(nd.ctrl, 0, sizeof(Ctrl), s));
-  if (nd.n_strips) HIPCHK(net, launch_strip_restore(nd, s));
   net->pinned_words = 0;
   HIPCHK(net, hipHostMalloc((void**)&net->pin_cb, kChunkRing * 8, hipHostMallocDefault));
   HIPCHK(net, hipHostMalloc((void**)&net->pin_rc, (size_t)nd.R * 4, hipHostMallocDefault));
@@ -2474,6 +2472,25 @@ snn_status build_impl(snn_net* net) {
     HIPCHK(net, copy_sync(net, net->d_addr, addr.data(), addr.size() * sizeof(float*), hipMemcpyHostToDevice));
     net->h_mbuf.resize((size_t)kGraphSteps * net->nch);
   }
+
+  // ---- what makes the steps faster, after all that the network needs ----
+  // the targets pull their input (kernels_pull.hip) unless a bin size was asked for
+  if (d_runs && !net->cfg.bin_capacity && !net->lean) {
+    if ((st = build_pull(net, pop_cls))) return st;
+  }
+  if (nd.n_pull) {
+    dev_free(net, d_runs);
+    nd.tile_runs = 1;
+  } else if (d_runs) {
+    uint32_t* d_rd; ALLOC(d_rd, uint32_t, n_runs);
+    HIPCHK(net, launch_runs(true, nd.grp_off, G, nd.payload, nd.cls_bits, nd.tile_shift, nullptr, d_runs, d_rd, nullptr, s));
+    nd.grp_run = d_runs; nd.run_desc = d_rd; nd.tile_runs = 1;
+  }
+  net->unit_shift = nd.n_tiles ? nd.tile_shift : 6u;
+  if (!nd.n_tiles && !net->has_adex && !nd.n_rules && !(net->cfg.flags & SNN_F_DELIVERY_DIRECT) &&
+      ((st = build_small(net, pop_cls)) || (!nd.small_row && (st = build_strips(net)))))
+    return st;
+  if (nd.n_strips) HIPCHK(net, launch_strip_restore(nd, s));
   HIPCHK(net, hipStreamSynchronize(s));
 #undef ALLOC
   net->built = true;
@@ -3039,6 +3056,8 @@ void net_set_allocator(snn_net* net, const snn_device& dev, bool have_dev) {
 }
 
 int net_device(const snn_net* net) { return net->device; }
+
+bool net_extra_alloc(const snn_net* net) { return net->extra; }
 
 bool net_is_fresh(const snn_net* net) { return !net->built && !net->released && net->N > 0; }
 

@@ -14,6 +14,8 @@ void net_set_allocator(snn_net* net, const snn_device& dev, bool have_dev);
 int net_device(const snn_net* net);
 // defined, not yet built, never released
 bool net_is_fresh(const snn_net* net);
+// whether the memory it asks its provider for now is such as it can do without
+bool net_extra_alloc(const snn_net* net);
 // synapses its projections will make (4 bytes each at least on the device)
 uint64_t net_planned_synapses(const snn_net* net);
 

@@ -45,6 +45,7 @@ struct Job;
 
 struct snn_server {
   size_t budget = 0;
+  size_t share = 0;  // budget / slots: a request takes memory that only makes it faster up to this
   std::mutex mu;
   std::condition_variable cv;
   std::deque<Job*> queue;                                  // submission order
@@ -77,13 +78,18 @@ struct Job {
   double t_submit = 0, t_start = 0, t_done = 0;
 };
 
-// Device memory of a served network: granted only within the budget.
+// Device memory of a served network: granted only within the budget, and what
+// the network can do without only within a slot's share of it, so that it does
+// not keep other requests waiting (two networks of 840,000 synapses under a budget
+// for both without their strips ran one after the other).
 void* srv_alloc(size_t bytes, void* user) {
   Job* j = static_cast<Job*>(user);
   snn_server* s = j->srv;
   {
     std::lock_guard<std::mutex> lk(s->mu);
-    if (s->in_use + bytes > s->budget) {
+    if (snn::net_extra_alloc(j->net)) {
+      if (j->bytes + bytes > s->share || s->in_use + bytes > s->budget) return nullptr;
+    } else if (s->in_use + bytes > s->budget) {
       j->refused = true;
       j->need = j->bytes + bytes;
       return nullptr;
@@ -199,6 +205,7 @@ snn_status snn_server_create(size_t hbm_budget, uint32_t slots, snn_server** out
   snn_server* s = new (std::nothrow) snn_server();
   if (!s) return SNN_E_NOMEM;
   s->budget = hbm_budget;
+  s->share = hbm_budget / slots;
   try {
     for (uint32_t k = 0; k < slots; ++k) s->workers.emplace_back(worker, s);
   } catch (...) {

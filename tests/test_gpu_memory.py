@@ -145,3 +145,22 @@ def test_served_network_without_device_memory_fails_as_such(snn):
     finally:
         srv.close()
         net.close()
+
+
+def test_extra_memory_keeps_no_request_waiting(snn):
+    """A budget for two networks without their strips: each is built at once."""
+    spec = lambda: [brunel(2100, 400)]
+    al = budget_allocator(snn, 1 << 40)
+    snn.Net(spec(), allocator=al, delivery="direct").close()
+    nets = [snn.Net(spec(), build=False) for _ in range(2)]
+    srv = Server(snn, 2 * al.peak + (1 << 20), 2)
+    try:
+        tickets = [srv.submit(net, 20000) for net in nets]
+        for net, t in zip(nets, tickets):
+            info = srv.result(t)
+            assert info.status == 0 and info.attempts == 1
+        assert all(np.array_equal(a, b) for a, b in zip(nets[0].spikes(), nets[1].spikes()))
+    finally:
+        srv.close()
+        for net in nets:
+            net.close()
