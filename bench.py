@@ -43,7 +43,8 @@ HBM_PEAK_GBS = 8000.0
 #  - per neuron: its state read and written (LIF: V, refractory count,
 #    P synaptic currents; AdEx: V, w, h, P conductances) and I_e read;
 #    direct delivery (not by strips) also reads its P int64 inputs.
-BYTES_PER_EVENT = {"k_step": 4 + 16, "k_step_binned": 4 + 8, "k_step_strip": 4 + 8, "k_pull": 2, "k_small": 4}
+BYTES_PER_EVENT = {"k_step": 4 + 16, "k_step_binned": 4 + 8, "k_step_binned_runs": 4 + 8, "k_step_strip": 4 + 8,
+                   "k_pull": 2, "k_small": 4}
 FP32_PEAK_TFLOPS = 157.3
 
 
@@ -89,17 +90,6 @@ def measured_traffic(workload: str, kernel: str, tile_neurons: int = 0, runs: st
     return ent["bytes_per_launch"]
 
 
-def step_kernel(net, specs: list, c: dict, config: dict) -> str:
-    """The kernel that runs the steps of a network with counters c, built with
-    `config`: as the library chooses it for the workloads here."""
-    if c["delivery"] == 2:
-        return "k_pull" if c.get("tile_runs") and not config.get("bin_capacity") else "k_step_binned"
-    adex = any(p["model"].startswith("aeif") for sp in specs for p in sp["populations"])
-    if config.get("delivery", "auto") != "auto" or adex:
-        return "k_step"
-    return "k_small" if c["n_neurons"] <= 2048 else "k_step_strip"
-
-
 def bytes_per_step_neurons(spec: dict, delivery: str) -> int:
     tot = 0
     for p in spec["populations"]:
@@ -119,7 +109,7 @@ def bytes_per_step_neurons(spec: dict, delivery: str) -> int:
 
 
 def step_roofline(net, specs: list, mode: str, steps: int, c0: dict, c1: dict, profile_steps: int,
-                  workload: str, config: dict) -> dict:
+                  workload: str) -> dict:
     """HBM roofline of the step kernel over the timed region: the algorithmic
     bytes of those steps (per-neuron state, per event, per selected pair, per
     spike) over the device time per step, measured with HIP events recorded on
@@ -136,7 +126,7 @@ def step_roofline(net, specs: list, mode: str, steps: int, c0: dict, c1: dict, p
     c2 = net.counters()
     prof = net.profile(profile_steps) if profile_steps > 0 else {"step": 0.0}
     iso_ms = prof["step"] / max(1, profile_steps)
-    kernel = step_kernel(net, specs, c2, config)
+    kernel = net.step_kernel()
     neuron_bytes = sum(bytes_per_step_neurons(sp, "direct" if kernel == "k_step" else "binned") for sp in specs)
     dlv_bytes = neuron_bytes + ev_p * BYTES_PER_EVENT[kernel] + pr_p * BYTES_PER_PAIR + sp_p * BYTES_PER_SPIKE
     achieved = dlv_bytes / (dev_ms * 1e-3) / 1e9 if dev_ms > 0 else 0.0
@@ -320,7 +310,7 @@ def main():
 
     c2 = net.counters()
     traffic_key = args.workload + ("_weight_sd" if args.weight_sd > 0 else "")
-    roofline = step_roofline(net, [spec], mode, args.steps, c0, c1, args.profile_steps, traffic_key, kw)
+    roofline = step_roofline(net, [spec], mode, args.steps, c0, c1, args.profile_steps, traffic_key)
     dlv_ms = roofline["avg_launch_us"] * 1e-3
     out = {
         "metric": METRIC,
@@ -468,7 +458,7 @@ def bench_sweep(args, S, W, torch):
     events = c1["events"] - c0["events"]
     print(f"[bench] batch: {steps} steps in {wall:.3f} s; profiling {args.profile_steps} steps", file=sys.stderr,
           flush=True)
-    roofline = step_roofline(net, specs, mode, args.steps, c0, c1, args.profile_steps, "sweep", kw)
+    roofline = step_roofline(net, specs, mode, args.steps, c0, c1, args.profile_steps, "sweep")
     print("[bench] sequential sample next", file=sys.stderr, flush=True)
     net.close()
     del net

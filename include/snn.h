@@ -427,6 +427,13 @@ snn_status snn_get_spikes(snn_net* net, uint64_t step_lo, uint64_t step_hi, uint
                           uint32_t* mult, size_t cap, size_t* n_out);
 /* Counters (see snn_counters). */
 snn_status snn_get_counters(snn_net* net, snn_counters* out);
+/* The kernel that runs the network's steps, chosen by snn_build (and kept after
+   snn_release; "" before): "k_small" (one block runs many steps of a small LIF
+   network), "k_step_strip" (direct delivery, by strips of targets), "k_step"
+   (direct, by device atomics), "k_step_binned", "k_step_binned_runs" (its count
+   pass reads tile runs) or "k_pull" (the targets pull their input; with
+   k_pull_update).  Results do not depend on it. */
+const char* snn_step_kernel(const snn_net* net);
 /* Integer input already delivered for the next step of gids [first, first+n)
    on `port` (network synapses only, Poisson excluded), in units of
    2^-shift(gid, port) of the weight unit. */

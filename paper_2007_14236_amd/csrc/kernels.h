@@ -85,6 +85,7 @@ hipError_t launch_runs(bool fill, const uint64_t* grp_off, uint64_t n_groups, co
 // the kernel's own dispatch.
 hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start = nullptr,
                        hipEvent_t stop = nullptr);
+const char* step_kernel(const NetDev& nd);  // the one it launches (or "k_small")
 // Pulled delivery (LIF networks with nd.n_pull): one step, the run index and the
 // 16-bit synapses of one instance (sets *too_long for a group of kRunMaxGroup synapses or more),
 // the waiting input into acc[buf], and what a restored snapshot needs: waiting

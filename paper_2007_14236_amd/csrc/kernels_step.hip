@@ -43,6 +43,14 @@ __global__ void __launch_bounds__(kB) k_pending_input(NetDev nd, uint32_t buf, u
 
 }  // namespace
 
+const char* step_kernel(const NetDev& nd) {
+  if (nd.small_row) return "k_small";
+  if (nd.n_pull) return "k_pull";
+  if (nd.n_strips) return "k_step_strip";
+  if (!nd.n_tiles) return "k_step";
+  return nd.tile_runs ? "k_step_binned_runs" : "k_step_binned";
+}
+
 hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 blk(kB), grid((nd.n_tiles ? nd.n_tiles : nd.nblk_upd) + nd.sel_grid);
   const bool lif = nd.pad0 & 1u, adex = nd.pad0 & 2u, beta = nd.pad0 & 4u;

@@ -299,6 +299,7 @@ struct snn_net {
   // snn_release: device memory returned, raster and counters kept on the host
   bool released = false;
   snn_counters final_ctr{};
+  const char* kernel = "";  // snn_step_kernel
 };
 
 namespace {
@@ -1334,6 +1335,7 @@ snn_status snn_build(snn_net* net) {
   if (st != SNN_OK) {
     const std::string msg = net->err;
     release_build(net);
+    net->kernel = "";
     net->err = msg;
   }
   return st;
@@ -2494,6 +2496,7 @@ snn_status build_impl(snn_net* net) {
   HIPCHK(net, hipStreamSynchronize(s));
 #undef ALLOC
   net->built = true;
+  net->kernel = step_kernel(nd);
   net->cur_step = net->drained_step = 0;
   st = build_graphs(net);
   if (st) return st;
@@ -2675,6 +2678,8 @@ snn_status snn_get_counters(snn_net* net, snn_counters* out) {
   out->tile_window = net->nd.tile_win;
   return leave(net);
 }
+
+const char* snn_step_kernel(const snn_net* net) { return net ? net->kernel : ""; }
 
 snn_status snn_get_input(snn_net* net, uint32_t first, uint32_t n, uint32_t port, int64_t* out) {
   if (!net || !out) return SNN_E_INVALID;

@@ -128,6 +128,7 @@ _SIGS = {
     "snn_get_spikes": (C.c_int32, [_P, C.c_uint64, C.c_uint64, C.POINTER(C.c_uint64), C.POINTER(C.c_uint32),
                                    C.POINTER(C.c_uint32), C.c_size_t, C.POINTER(C.c_size_t)]),
     "snn_get_counters": (C.c_int32, [_P, C.POINTER(Counters)]),
+    "snn_step_kernel": (C.c_char_p, [_P]),
     "snn_get_input": (C.c_int32, [_P, C.c_uint32, C.c_uint32, C.c_uint32, C.POINTER(C.c_int64)]),
     "snn_get_input_noalloc": (C.c_int32, [_P, C.c_uint32, C.c_uint32, C.c_uint32, C.POINTER(C.c_int64)]),
     "snn_get_shift": (C.c_int32, [_P, C.c_uint32, C.c_uint32, C.POINTER(C.c_int32)]),
@@ -435,6 +436,10 @@ class Net:
         c = Counters()
         self._check(self.L.snn_get_counters(self.h, C.byref(c)))
         return c.as_dict()
+
+    def step_kernel(self) -> str:
+        """Name of the kernel that runs the network's steps (chosen by the build)."""
+        return self.L.snn_step_kernel(self.h).decode()
 
     def get_input(self, port: int = 0, first: int = 0, n: int | None = None) -> np.ndarray:
         n = self.N - first if n is None else n
