@@ -179,7 +179,8 @@ typedef struct snn_counters {
                                tile they reach and delivery reads an index of
                                these runs: the targets pull their input along it
                                (at most 4 weight classes onto a neuron, no bin
-                               size asked for), or the bins' count pass reads
+                               size and no tile of at most 512 neurons asked
+                               for), or the bins' count pass reads
                                them (4 bytes per run, 8 per group) instead of
                                every synapse word                             */
   uint32_t tile_window;     /* binned: 1 when every tile overlaps at most 8

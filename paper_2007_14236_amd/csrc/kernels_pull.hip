@@ -20,20 +20,28 @@
 // is 16 bits here (target within the tile and which count), made from the
 // 32-bit words at build.
 //
-// Step n is two kernels.  k_pull_update: block = slice of up to 4,096 neurons;
+// Step n is two kernels.  k_pull_update: block = slice of 512 to 4,096 neurons;
 // input of step n from the counts, update, emission, the range of the slice's
 // spikes in the step.  k_pull: every delay >= 1 into the counts of step n + 1
 // (the records of step n are complete by then).  The work of k_pull follows
 // the spikes, which differ by a factor of ten and more between the instances
-// of a sweep: a tile is split into parts of about kUnitEvents events, which
-// blocks take from a queue and whose counts the update adds up.
+// of a sweep and between a quiet step and a volley: a tile is split into parts by
+// the step's events, about two parts to a block, which blocks take from a queue
+// and whose counts the update adds up.  A part of fewer than 2,048 events costs
+// more to clear, write and add up than it saves.
 //
 // Measured on 128 Brunel instances (3.0 10^6 neurons, 10^8 events a step):
 // through bins 769 us a step; pulled with int64 sums of 4,096-neuron tiles
 // 1,068 us; with 16-bit counts of 16,384-neuron tiles from the 32-bit words
 // 350 us (245 in k_pull, 1.03 GB fetched at 4.2 TB/s, lines of 128 B of runs
 // of ~54); with the 16-bit synapses and 32,768-neuron tiles 305 us (206 in
-// k_pull, 0.57 GB fetched; bound by the latency of the runs, 16 waves a CU).
+// k_pull, 0.57 GB fetched; bound by the latency of the runs, 16 waves a CU); with
+// full batches of runs and parts by the step's events 257.
+// With parts of 196,608 events and slices of 4,096 neurons whatever the network,
+// few events left most CUs without any.  Us a step through bins, so, and now: 120,000
+// neurons with 5,000 synapses and 240,000 events a step 52, 165, 29; ten networks of
+// 25,000 and 2,500, 230,000 events 57, 99, 32; 60,000 and 10,000, 340,000 events 61,
+// 152, 31; the 77,169-neuron microcircuit, 130,000 events 68, 129, 42.
 #include "step_dev.h"
 
 namespace snn {
@@ -44,11 +52,16 @@ constexpr int kT = 1024;            // threads of a k_pull block
 constexpr int kWaves = kT / 64;
 constexpr int kUT = 512;            // threads of a k_pull_update block
 constexpr int kUpdN = kPullSlice / kUT;
-constexpr uint32_t kUnitEvents = 196608;  // events of a part of a tile
-constexpr int kBatch = 32;          // spikes of a wave's batch: their runs are all in flight at once
+static_assert(kUT == kPullRow, "a row of a slice is a neuron a thread");
+constexpr uint32_t kUnits = 2 * kPullGrid;  // parts of tiles, about, where there are many events
+// ... of at least this many, in 1,024s: 2, 4 and 16 for the microcircuit 42, 41 and 48 us
+// a step, at 0.37 of its size (5,700 events) 30, 32 and 36
+constexpr uint32_t kUnitMin = 2;
+constexpr int kBatch = 32;          // spikes of a wave's batch, at most: their runs are all in flight at once
 constexpr int kRunLanes = 16;       // lanes that share a run
 constexpr int kGroups = 64 / kRunLanes;
 constexpr int kU = 8;
+constexpr int kDelays = 16;         // spike counts of a tile's instance in flight at once
 
 // Counts of neuron i (nw words) of its tile's parts, as the int64 input a[].
 __device__ __forceinline__ void pull_input(const NetDev& nd, const PullPop& pw, uint32_t i, uint32_t parts, int64_t* a) {
@@ -106,7 +119,7 @@ __global__ void __launch_bounds__(kUT, 6) k_pull_update(NetDev nd, uint32_t rel)
   static_assert(kUpdN <= 8, "a byte of mq per neuron");
   bool mover = false;
 #pragma unroll 1
-  for (int q = 0; q < kUpdN; ++q) {
+  for (int q = 0; q * kUT < (int)nt; ++q) {
     const uint32_t loc = q * kUT + threadIdx.x;
     if (loc < nt) {
       const uint32_t i = first + loc;
@@ -134,7 +147,7 @@ __global__ void __launch_bounds__(kUT, 6) k_pull_update(NetDev nd, uint32_t rel)
   uint32_t before[kUpdN], spikes = 0;  // spikes of the (row, wave)s ahead of this wave's
 #pragma unroll
   for (int q = 0; q < kUpdN; ++q)
-    for (int w = 0; w < (kUT / 64); ++w) {
+    for (int w = 0; w < (kUT / 64) && q * kUT < (int)nt; ++w) {
       if (w == wv) before[q] = spikes;
       spikes += sl.wcnt[q][w];
     }
@@ -188,17 +201,18 @@ __device__ __forceinline__ uint32_t scan_excl(uint32_t v, uint32_t* lds, uint32_
 struct PullLds {
   uint32_t cnt[kPullWords];          // counts of the tile
   uint32_t unit0[kPullMaxTiles];     // first unit of each tile
-  uint32_t bat0[kT];                 // first batch of each segment of the unit
-  SpkRange rng[kT];                  // a segment's spikes
+  uint32_t item0[kT];                // first item of each segment of the unit
+  uint32_t spk0[kT];                 // a segment's first spike
   uint32_t red[kWaves];
   uint32_t unit;                     // the block's unit, from the queue
 };
 
 // Input of step n + 1.  Units: part q of tile t, for the parts of each tile;
 // blocks take them from the step's queue.  A unit's segments are the (delay, source
-// slice) pairs whose number is q modulo the tile's parts; their spikes are cut
-// into batches of kBatch, one wave each: its lanes find the runs, then groups
-// of kRunLanes lanes take them, kU runs in flight per group.
+// slice) pairs whose number is q modulo the tile's parts; their spikes, segment
+// after segment, are cut into batches of up to kBatch, one wave each: its lanes
+// find the runs, then groups of kRunLanes lanes take them, kU runs in flight per
+// group.
 __global__ void __launch_bounds__(kT) k_pull(NetDev nd, uint32_t rel) {
   __shared__ PullLds sh;
   const uint64_t n = nd.ctrl->step_base + rel;
@@ -207,17 +221,27 @@ __global__ void __launch_bounds__(kT) k_pull(NetDev nd, uint32_t rel) {
   // parts of every tile, from the spikes in flight of its instance
   uint32_t units = 0, mine = 0;
   {
-    uint32_t parts = 0;
+    uint32_t parts = 0, ev = 0, all, segs = 0;  // ev: the tile's events, in 1,024s
     if (threadIdx.x < ntile) {
       const PullTile tl = nd.pull_tile[threadIdx.x];
       uint64_t items = 0;
-      for (uint32_t d = 1; d <= ndel; ++d) {
-        const uint32_t slot = slot0 >= d ? slot0 - d : slot0 + nd.R - d;
-        items += nd.inst_spk[(size_t)slot * nd.n_pull + tl.inst];
+      for (uint32_t d0 = 1; d0 <= ndel; d0 += kDelays) {
+        uint32_t c[kDelays];
+#pragma unroll
+        for (int q = 0; q < kDelays; ++q) {
+          const uint32_t d = d0 + q, slot = slot0 >= d ? slot0 - d : slot0 + nd.R - d;
+          c[q] = d <= ndel ? nd.inst_spk[(size_t)slot * nd.n_pull + tl.inst] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < kDelays; ++q) items += c[q];
       }
-      const uint64_t ev = (uint64_t)((float)items * tl.mean_run);
-      parts = (uint32_t)min((uint64_t)kPullParts, ev / kUnitEvents + 1);
-      parts = min(parts, ndel * nd.pull_inst[tl.inst].ns);  // a segment a part at least
+      ev = (uint32_t)fminf((float)items * tl.mean_run * (1.f / 1024.f), 4194304.f);
+      segs = ndel * nd.pull_inst[tl.inst].ns;
+    }
+    (void)scan_excl(ev, sh.red, &all);
+    if (threadIdx.x < ntile) {
+      const uint32_t unit = max(all / kUnits, kUnitMin);
+      parts = min(min((uint32_t)kPullParts, ev / unit + 1), segs);  // a segment a part at least
       if (blockIdx.x == 0) nd.pull_parts[threadIdx.x] = parts;
     }
     mine = scan_excl(parts, sh.red, &units);
@@ -260,24 +284,25 @@ __global__ void __launch_bounds__(kT) k_pull(NetDev nd, uint32_t rel) {
         const uint32_t d = s / pi.ns + 1, slot = slot0 >= d ? slot0 - d : slot0 + nd.R - d;
         r = nd.slice_spk[(size_t)slot * nd.n_slices + pi.s0 + s % pi.ns];
       }
-      uint32_t nbat;
-      const uint32_t b0 = scan_excl((r.end - r.begin + kBatch - 1) / kBatch, sh.red, &nbat);
-      sh.bat0[threadIdx.x] = b0;
-      sh.rng[threadIdx.x] = r;
+      uint32_t nitem;
+      const uint32_t i0 = scan_excl(r.end - r.begin, sh.red, &nitem);
+      sh.item0[threadIdx.x] = i0;
+      sh.spk0[threadIdx.x] = r.begin;
       __syncthreads();
-      for (uint32_t b = wv; b < nbat; b += kWaves) {  // wave-uniform
-        uint32_t sl = 0, sr = kT;  // the last segment that starts at or before batch b
-        while (sr - sl > 1) {
-          const uint32_t mid = (sl + sr) >> 1;
-          if (sh.bat0[mid] <= b) sl = mid; else sr = mid;
-        }
-        sl = __builtin_amdgcn_readfirstlane(sl);
-        const uint32_t sg = s0 + sl * parts, d = sg / pi.ns + 1;
-        const uint32_t slot = slot0 >= d ? slot0 - d : slot0 + nd.R - d;
-        const uint32_t x = sh.rng[sl].begin + (b - sh.bat0[sl]) * kBatch + lane;
+      // a wave's batch: few items go to all the waves
+      const uint32_t bat = min((uint32_t)kBatch, max((uint32_t)kGroups, (nitem + kWaves - 1) / kWaves));
+      for (uint32_t b = wv * bat; b < nitem; b += kWaves * bat) {  // wave-uniform
+        const uint32_t x = b + lane;
         uint32_t off = 0, lm = 0;  // first synapse of the lane's run; length | multiplicity << kRunLenBits
-        if (lane < kBatch && x < sh.rng[sl].end) {
-          const SpikeRec rec = nd.recent[(size_t)slot * nd.N + x];
+        if (lane < bat && x < nitem) {
+          uint32_t sl = 0, sr = kT;  // the last segment that starts at or before item x
+          while (sr - sl > 1) {
+            const uint32_t mid = (sl + sr) >> 1;
+            if (sh.item0[mid] <= x) sl = mid; else sr = mid;
+          }
+          const uint32_t d = (s0 + sl * parts) / pi.ns + 1;
+          const uint32_t slot = slot0 >= d ? slot0 - d : slot0 + nd.R - d;
+          const SpikeRec rec = nd.recent[(size_t)slot * nd.N + sh.spk0[sl] + (x - sh.item0[sl])];
           if ((rec.mask >> d) & 1ull) {
             const uint32_t g = rec.grp_ptr + (uint32_t)__popcll(rec.mask & ((1ull << d) - 1ull)) - pi.g0;
             const uint32_t* e = row + (size_t)g * pi.nt;

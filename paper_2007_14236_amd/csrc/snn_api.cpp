@@ -40,6 +40,8 @@ constexpr uint64_t kSmallSyn = 1u << 19;           // small networks: synapses, 
 constexpr uint32_t kStripGrid = 256;               // strips, about
 constexpr uint64_t kStripFree = 64ull << 20;       // ... bytes of their index, and of their spill, not weighed
 constexpr uint32_t kSmallPops = 16;                // ... populations
+constexpr uint32_t kPullTile = 512;  // pulled delivery beyond tiles of this many neurons that were asked for
+constexpr uint32_t kPullUpd = 768;   // blocks of the pulled update that the chip holds at once
 constexpr uint64_t kPullMinMean = 4; // pulled delivery when the (group, tile) runs average this many synapses
 constexpr uint64_t kRunMinMean = 4;  // tile runs when groups average this many synapses per touched tile
 constexpr uint64_t kQueueMinInstances = 8;          // binned batches with at least this many instances ...
@@ -1515,6 +1517,9 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
   std::vector<PullSlice> sl;
   std::vector<PullTile> tl;
   uint64_t rows = 0, syn0 = 0, pay0 = 0;
+  // neurons of a slice: whole rows of a block, no more than give every place on the
+  // chip a block (slices of 4,096 left it to 19 blocks for 77,169 neurons: 50 us, now 12)
+  const uint32_t slice = (uint32_t)std::min<uint64_t>(kPullSlice, (nd.N / ((uint64_t)kPullRow * kPullUpd) + 1) * kPullRow);
   for (size_t i = 0; i < ni; ++i) {
     PullInst& p = pi[i];
     memset(&p, 0, sizeof p);
@@ -1524,8 +1529,8 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
     p.s0 = (uint32_t)sl.size(); p.t0 = (uint32_t)tl.size();
     syn0 += syn[i];
     pay0 += (syn[i] + 1) & ~1ull;
-    const uint32_t per = kPullWords / kPullSlice / nw;  // slices of a tile, at most
-    p.ns = (n + kPullSlice - 1) / kPullSlice;
+    const uint32_t per = kPullWords / nw / slice;  // slices of a tile, at most
+    p.ns = (n + slice - 1) / slice;
     p.nt = (p.ns + per - 1) / per;
     for (uint32_t t = 0, q = 0; t < p.nt; ++t) {  // slices of equal size, tiles of equal numbers of them
       PullTile x;
@@ -2476,8 +2481,13 @@ snn_status build_impl(snn_net* net) {
   }
 
   // ---- what makes the steps faster, after all that the network needs ----
-  // the targets pull their input (kernels_pull.hip) unless a bin size was asked for
-  if (d_runs && !net->cfg.bin_capacity && !net->lean) {
+  // the targets pull their input (kernels_pull.hip) unless a bin size was asked for, or
+  // tiles of at most 512 neurons: a pulled step has the same blocks whatever the tiles,
+  // bins have one a tile, and more of them are faster.  Us a step, bins and pulled:
+  // 1,000 neurons with 300 synapses, ten times, tiles of 256: 17, 20; 10,000 with
+  // 1,000: 14, 31; of 512: 18, 26; 2,500 with 300, tiles of 1,024: 21, 19; 3,000 with
+  // 300, thirty times: 28, 25; 10,000 with 1,000, tiles of 4,096: 52, 23
+  if (d_runs && !net->cfg.bin_capacity && !(net->cfg.tile_neurons && net->cfg.tile_neurons <= kPullTile) && !net->lean) {
     if ((st = build_pull(net, pop_cls))) return st;
   }
   if (nd.n_pull) {

@@ -159,6 +159,7 @@ constexpr uint32_t kTilePopLds = 8;
 // slices of at most kPullSlice neurons (a block of the update) and these into
 // tiles of at most kPullWords 32-bit words of counts (a block's LDS).
 constexpr int kPullSlice = 4096;
+constexpr int kPullRow = 512;              // neurons that a block of the update takes at once
 constexpr int kPullWords = 32768;
 constexpr int kPullSlots = 4;              // weight classes onto a neuron, 16-bit counts, two to a word
 constexpr int kPullParts = 24;             // most parts of a tile
