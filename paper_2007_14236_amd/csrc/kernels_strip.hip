@@ -1,7 +1,7 @@
 // kernels_strip.hip -- LIF networks with direct delivery: every strip of
 // neurons takes its own input.
 //
-// The network is cut into strips of 64 .. 1024 consecutive neurons, a block
+// The network is cut into strips of 32 .. 1024 consecutive neurons, a block
 // each.  In step n a block reads the spikes of step n - 1 and, from rows by
 // (source, strip), their synapses onto its neurons: those of delay 1 go into the
 // strip's input in LDS, the others into the strip's own lists of events by
@@ -498,7 +498,7 @@ constexpr int kRowRegs = 16;
 constexpr int kRT = 512;
 constexpr uint32_t kRowWords = kRowRegs * kRT;
 
-__global__ void __launch_bounds__(kRT) k_strip_rows(NetDev nd, uint32_t magic, uint32_t* row, uint32_t* pay, uint32_t* deg) {
+__global__ void __launch_bounds__(kRT) k_strip_rows(NetDev nd, uint32_t shift, uint32_t magic, uint32_t* row, uint32_t* pay, uint32_t* deg) {
   __shared__ uint64_t red[kRT / 64];
   __shared__ uint32_t cnt[kStripMax], stage[kRowWords];
   const uint32_t s = blockIdx.x, S = nd.n_strips, g0 = nd.grp_ptr[s], cls_mask = (1u << nd.cls_bits) - 1u;
@@ -520,9 +520,9 @@ __global__ void __launch_bounds__(kRT) k_strip_rows(NetDev nd, uint32_t magic, u
   const uint32_t begin = (uint32_t)(nd.grp_off[g0 + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] - o);
   for (uint32_t k = threadIdx.x; k < S; k += kRT) cnt[k] = 0;
   __syncthreads();
-  // strip of a target: a quotient of 64s by multiplication, 24 bits wide; exact
-  // while (N / 64) (strip_n / 64) < 2^20
-  auto strip = [&](uint32_t x) { return (uint32_t)__umul24(x >> (nd.cls_bits + 6), magic) >> 20; };
+  // strip of a target: a quotient of 64s (or, alone, 32s) by multiplication, 24 bits
+  // wide; exact while (N / 64) (strip_n / 64) < 2^20
+  auto strip = [&](uint32_t x) { return (uint32_t)__umul24(x >> (nd.cls_bits + shift), magic) >> 20; };
   // delay of word j, consecutive words j - lane on in a wave (all its lanes)
   auto delay = [&](uint32_t j) {
     const uint32_t j0 = __builtin_amdgcn_readfirstlane(j);
@@ -617,8 +617,9 @@ hipError_t launch_strip_restore(const NetDev& nd, hipStream_t s) {
 }
 
 hipError_t launch_strip_rows(const NetDev& nd, uint32_t* row, uint32_t* pay, uint32_t* deg, hipStream_t s) {
-  const uint32_t u = nd.strip_n / 64, magic = ((1u << 20) + u - 1) / u;
-  hipLaunchKernelGGL(k_strip_rows, dim3(nd.N), dim3(kRT), 0, s, nd, magic, row, pay, deg);
+  const uint32_t shift = nd.strip_n < 64 ? 5 : 6;
+  const uint32_t u = nd.strip_n >> shift, magic = ((1u << 20) + u - 1) / u;
+  hipLaunchKernelGGL(k_strip_rows, dim3(nd.N), dim3(kRT), 0, s, nd, shift, magic, row, pay, deg);
   return hipGetLastError();
 }
 

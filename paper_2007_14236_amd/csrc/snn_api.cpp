@@ -1444,7 +1444,13 @@ snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& p
 }
 
 // Strips (kernels_strip.hip), for direct delivery of LIF networks that are not
-// small, without plastic synapses: about a strip per CU, of at least a wave.  They
+// small, without plastic synapses: about a strip per CU, of at least half a wave
+// (a strip takes 3.4 ns an event beyond its 6 us: strips of 64 were slower than device
+// atomics where a step brings 1,000 events and more onto each of few strips.  Us a
+// step by atomics, strips of 64 and of 32: 1,000 neurons with 1,000 synapses and 33,000
+// events a step 11.2, 13.1, 9.8; 3,000 and 3,000, 300,000: 25, 27, 19; 500
+// generators onto 500 neurons, 40,000: 16.4, 23.2, 15.4; 800 onto 1,000, 480,000: 78,
+// 110, 62.  Quiet networks of 2,100 neurons 5.0, 4.2, 4.3, and 4.6 with strips of 16).  They
 // were the faster way at every size tried (2,100 .. 450,000 neurons, 50 .. 4,000
 // synapses each; the figures stand there), so only memory draws the line: the row
 // index and the spill not beyond the synapses themselves (300,000 neurons with 30
@@ -1456,7 +1462,8 @@ snn_status build_strips(snn_net* net) {
   const NetDev& nd = net->nd;
   NetDev x = nd;
   hipStream_t s = net->stream;
-  x.strip_n = std::min<uint32_t>(kStripN, std::max<uint32_t>(64, ((nd.N + kStripGrid - 1) / kStripGrid + 63) / 64 * 64));
+  const uint32_t per = (nd.N + kStripGrid - 1) / kStripGrid;
+  x.strip_n = per <= 32 ? 32 : std::min<uint32_t>(kStripN, (per + 63) / 64 * 64);
   const uint64_t S = (nd.N + x.strip_n - 1) / x.strip_n;
   const uint64_t rows = (uint64_t)nd.N * (S + 1), spill = (uint64_t)nd.R * nd.N * nd.P;
   if (net->lean || S > kStripMax || !nd.n_syn || nd.n_syn >> 32 || nd.npop > kStripPops || nd.npois > kStripPois) return SNN_OK;
@@ -1466,7 +1473,7 @@ snn_status build_strips(snn_net* net) {
   const double run = (double)nd.n_syn / (double)(nd.N * S);  // synapses of a source onto a strip, mean
   x.strip_lanes = 0;
   while (x.strip_lanes < 6 && (double)(1u << x.strip_lanes) < run + 2.0 * std::sqrt(run)) ++x.strip_lanes;
-  x.strip_cap = (uint32_t)std::max<uint64_t>(256, nd.n_syn / (S * nd.R * 4));
+  x.strip_cap = (uint32_t)std::max<uint64_t>(std::min<uint32_t>(256, 4 * x.strip_n), nd.n_syn / (S * nd.R * 4));
   const size_t old = net->allocs.size();
   uint32_t* d_row = dalloc<uint32_t>(net, rows);
   uint32_t* d_pay = dalloc<uint32_t>(net, nd.n_syn);
@@ -2502,7 +2509,10 @@ snn_status build_impl(snn_net* net) {
   if (!nd.n_tiles && !net->has_adex && !nd.n_rules && !(net->cfg.flags & SNN_F_DELIVERY_DIRECT) &&
       ((st = build_small(net, pop_cls)) || (!nd.small_row && (st = build_strips(net)))))
     return st;
-  if (nd.n_strips) HIPCHK(net, launch_strip_restore(nd, s));
+  if (nd.n_strips) {
+    if (nd.strip_n < 64) net->unit_shift = 5;  // a wave holds one strip's neurons
+    HIPCHK(net, launch_strip_restore(nd, s));
+  }
   HIPCHK(net, hipStreamSynchronize(s));
 #undef ALLOC
   net->built = true;

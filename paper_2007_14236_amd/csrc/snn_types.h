@@ -169,7 +169,7 @@ constexpr uint32_t kPullGrid = 256;        // a block of k_pull on each CU
 // Small networks (small_row set): all steps of a launch in one block.
 constexpr uint32_t kSmallN = 2048;         // neurons, at most: two a thread
 constexpr size_t kSmallLds = 160 * 1024;   // LDS of a block
-// Strips (n_strips set): a neuron a thread, and the strips of a network.
+// Strips (n_strips set): a neuron a thread (strip_n 32 or whole waves), and the strips of a network.
 constexpr uint32_t kStripN = 1024;
 constexpr uint32_t kStripMax = 512;
 constexpr int kStripDelayShift = 10;       // synapse of a strip's row: local target << 16 | delay << 10 | class
