@@ -51,3 +51,16 @@ def test_generators_onto_few_neurons(snn, monkeypatch, targets):
             dict(name="L", model="lif_delta", n=targets, ports=1, params=lif, V0=np.linspace(0.0, 19.0, targets), I_e=100.0)]
     projs = [dict(src="G", tgt="L", rule="fixed_outdegree", K=200, weight=0.02 * targets / 500, delay=("uniform", 0.1, 2.0), port=0)]
     check(snn, monkeypatch, [dict(name="few", dt=0.1, seed=3, dmax=25, populations=pops, projections=projs, poisson=[])])
+
+
+@pytest.mark.parametrize("delay", [("uniform", 0.1, 2.5), ("const", 0.1, 0.0), ("const", 0.7, 0.0)], ids=["many", "first", "one"])
+def test_rows_beyond_a_block(snn, monkeypatch, delay):
+    """Sources of 8,191, 8,192 and 8,193 synapses and of some 20,000, which are brought
+    to their strips in two ways; each source fires."""
+    lif = dict(tau_m=20.0, C_m=250.0, E_L=0.0, V_th=20.0, V_reset=10.0, t_ref=2.0)
+    pops = [dict(name=f"S{k}", model="lif_delta", n=3, ports=1, params=dict(lif), V0=np.array([3.0, 15.0, 19.9]), I_e=400.0)
+            for k in (8191, 8192, 8193, 20011)]
+    pops.append(dict(name="T", model="lif_delta", n=2501, ports=1, params=dict(lif), V0=np.linspace(0.0, 19.9, 2501), I_e=200.0))
+    projs = [dict(src=p["name"], tgt="T", rule="fixed_outdegree", K=int(p["name"][1:]), weight=w, delay=delay, port=0)
+             for p, w in zip(pops, (0.11, -0.07, 0.05, 0.02))]
+    check(snn, monkeypatch, [dict(name="rows", dt=0.1, seed=5, dmax=30, populations=pops, projections=projs, poisson=[])])
