@@ -88,14 +88,14 @@ hipError_t launch_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t
 const char* step_kernel(const NetDev& nd);  // the one it launches (or "k_small")
 // Pulled delivery (LIF networks with nd.n_pull): one step, the run index and the
 // 16-bit synapses of one instance (sets *too_long for a group of kRunMaxGroup synapses or more),
-// the waiting input into acc[buf], and what a restored snapshot needs: waiting
-// bins into acc[buf], records by slice (clears what the counts hold).
+// the waiting input into acc[buf], and what a restored snapshot needs: records by
+// slice (clears what the counts hold).
 void launch_pull_step(const NetDev& nd, uint32_t rel, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 hipError_t launch_pull_rows(const NetDev& nd, const PullInst& pi, uint64_t groups, uint32_t* row, uint32_t* too_long,
                             hipStream_t s);
 hipError_t launch_pull_pay(const NetDev& nd, const PullInst& pi, uint64_t syn, uint16_t* pay, hipStream_t s);
 hipError_t launch_pull_fold(const NetDev& nd, uint32_t buf, hipStream_t s);
-hipError_t launch_pull_restore(const NetDev& nd, uint32_t buf, hipStream_t s);
+hipError_t launch_pull_restore(const NetDev& nd, hipStream_t s);
 // Small LIF networks (kernels_small.hip): steps in one launch (advances the
 // step counter itself), what a readback needs, what a restored snapshot needs
 // (ring cleared by the caller), the rows of the sources, the LDS of a block.

@@ -412,27 +412,6 @@ __global__ void __launch_bounds__(kB) k_pull_pay(NetDev nd, PullInst pi, uint64_
   }
 }
 
-// After a restore: what delivery through bins left in the bins, added to
-// acc[buf] and the bins emptied (block per bin tile).
-__global__ void __launch_bounds__(kB) k_pull_take_bins(NetDev nd, uint32_t buf) {
-  const uint32_t t = blockIdx.x, first = t << nd.tile_shift;
-  const size_t ti = (size_t)buf * nd.n_tiles + t;
-  const uint32_t cnt = min(nd.bin_cnt[ti], nd.bin_cap[t]);
-  const uint32_t* bin = nd.bins + (size_t)buf * nd.bins_total + nd.bin_off[t];
-  for (uint32_t j = threadIdx.x; j < cnt; j += kB) {
-    const uint32_t e = bin[j], cls = e & (uint32_t)(kMaxClasses - 1), loc = e >> kBinLocalShift;
-    if (cls >= nd.n_classes || first + loc >= nd.N) continue;
-    const int64_t v = nd.cls_wq[cls] * (int64_t)((e >> kBinMultShift) & kMaxMult);
-    atomicAdd((unsigned long long*)&nd.acc[((size_t)buf * nd.N + first + loc) * nd.P + nd.cls_port[cls]],
-              (unsigned long long)v);
-  }
-  __syncthreads();
-  if (threadIdx.x < (uint32_t)kInBuf) {
-    nd.bin_cnt[(size_t)threadIdx.x * nd.n_tiles + t] = 0;
-    nd.ovf_flag[(size_t)threadIdx.x * nd.n_tiles + t] = 1u;
-  }
-}
-
 // After a restore: the records of one step slot put in the order of the
 // slices (any order within a step delivers the same), with the slices' ranges
 // and the instances' counts.  tmp: the slot's records as they were.
@@ -505,9 +484,8 @@ hipError_t launch_pull_pay(const NetDev& nd, const PullInst& pi, uint64_t syn, u
 // The records of a slot are put by in the counts, which the next step does not
 // read (its input lies in acc) and then writes.
 static_assert(kPullParts * sizeof(uint32_t) >= sizeof(SpikeRec), "N records fit the counts");
-hipError_t launch_pull_restore(const NetDev& nd, uint32_t buf, hipStream_t s) {
+hipError_t launch_pull_restore(const NetDev& nd, hipStream_t s) {
   SpikeRec* tmp = reinterpret_cast<SpikeRec*>(nd.pull_cnt);
-  hipLaunchKernelGGL(k_pull_take_bins, dim3(nd.n_tiles), dim3(kB), 0, s, nd, buf);
   for (uint32_t slot = 0; slot < nd.R; ++slot) {
     const hipError_t e = hipMemcpyAsync(tmp, nd.recent + (size_t)slot * nd.N, (size_t)nd.N * sizeof(SpikeRec),
                                         hipMemcpyDeviceToDevice, s);

@@ -82,7 +82,7 @@ hipError_t launch_advance(Ctrl* ctrl, uint32_t steps, hipStream_t s) {
 
 hipError_t launch_pending_input(const NetDev& nd, uint32_t buf, uint32_t first, uint32_t n, uint32_t port,
                                 int64_t* out, hipStream_t s) {
-  if (n == 0 || nd.n_tiles == 0) return hipSuccess;
+  if (n == 0 || nd.n_tiles == 0 || nd.n_pull) return hipSuccess;  // pulled: no bins
   const uint32_t t0 = first >> nd.tile_shift, t1 = (first + n - 1) >> nd.tile_shift;
   hipLaunchKernelGGL(k_pending_input, dim3(t1 - t0 + 1), dim3(kB), 0, s, nd, buf, first, n, port, out);
   return hipGetLastError();

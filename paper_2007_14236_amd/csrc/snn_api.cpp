@@ -281,6 +281,8 @@ struct snn_net {
   uint32_t* pinned = nullptr;   // staging of a window's ring entries
   size_t pinned_words = 0;
   uint32_t tile_neurons = 0;       // binned delivery (0: direct)
+  std::vector<uint64_t> bin_off;   // ... its bins
+  std::vector<uint32_t> bin_cap;
   size_t small_ring_bytes = 0;
   bool lean = false;               // build without the arrays that only make it or the steps faster
   bool extra = false;              // such an array is being allocated
@@ -543,7 +545,7 @@ struct SnapHeader {
   uint64_t n_tiles, bins_total, n_syn, n_groups, nblk, sel_grid, cur_step, bytes;
 };
 
-// The device arrays that change while simulating, with their sizes.
+// The device arrays that change while simulating, with their sizes (a null one: zeros).
 std::vector<std::pair<void*, size_t>> state_arrays(const snn_net* net) {
   const NetDev& nd = net->nd;
   const size_t N = nd.N, P = nd.P;
@@ -556,6 +558,7 @@ std::vector<std::pair<void*, size_t>> state_arrays(const snn_net* net) {
   add(nd.gen_next, N * 4);
   add(nd.acc, (size_t)kInBuf * N * P * 8);
   if (nd.n_tiles) {
+    if (nd.n_pull && nd.bins_total) a.push_back({nullptr, (size_t)kInBuf * nd.bins_total * 4});  // none there: all empty
     add(nd.bins, (size_t)kInBuf * nd.bins_total * 4);
     add(nd.bin_cnt, (size_t)kInBuf * nd.n_tiles * 4);
     add(nd.ovf_flag, (size_t)kInBuf * nd.n_tiles * 4);
@@ -571,6 +574,40 @@ std::vector<std::pair<void*, size_t>> state_arrays(const snn_net* net) {
     add(nd.last_post, N * 4); add(nd.arr_list, (size_t)2 * nd.n_plastic * 8); add(nd.arr_cnt, 8);
   }
   return a;
+}
+
+// The input buffers of a snapshot (its arrays at `in`) of a network that takes its
+// input from them alone, with the entries of the step's bins added; empty where
+// these hold none.
+std::vector<int64_t> pull_waiting_input(const snn_net* net, const char* in, uint64_t step) {
+  const NetDev& nd = net->nd;
+  const char *acc = nullptr, *bins = nullptr, *cnt = nullptr;
+  for (const auto& x : state_arrays(net)) {
+    if (x.first == nd.acc) acc = in;
+    else if (!x.first) bins = in;
+    else if (x.first == nd.bin_cnt) cnt = in;
+    in += x.second;
+  }
+  std::vector<int64_t> out;
+  const size_t buf = step % kInBuf, half = (size_t)nd.N * nd.P;
+  for (uint32_t t = 0; t < nd.n_tiles && bins; ++t) {
+    uint32_t n;
+    memcpy(&n, cnt + (buf * nd.n_tiles + t) * 4, 4);
+    n = std::min(n, net->bin_cap[t]);
+    if (n && out.empty()) {
+      out.resize(kInBuf * half);
+      memcpy(out.data(), acc, out.size() * 8);
+    }
+    for (uint32_t j = 0; j < n; ++j) {
+      uint32_t e;
+      memcpy(&e, bins + (buf * nd.bins_total + net->bin_off[t] + j) * 4, 4);
+      const uint32_t cls = e & (uint32_t)(kMaxClasses - 1);
+      const uint64_t tgt = ((uint64_t)t << nd.tile_shift) + (e >> kBinLocalShift);
+      if (cls >= nd.n_classes || tgt >= nd.N) continue;
+      out[buf * half + tgt * nd.P + net->cls_port[cls]] += net->cls_wq[cls] * (int64_t)((e >> kBinMultShift) & kMaxMult);
+    }
+  }
+  return out;
 }
 
 SnapHeader snap_header(const snn_net* net) {
@@ -1069,7 +1106,8 @@ snn_status snn_snapshot(snn_net* net, void* buf, size_t cap) {
   memcpy(out, &h, sizeof h);
   size_t off = sizeof h;
   for (const auto& x : state_arrays(net)) {
-    HIPCHK(net, copy_sync(net, out + off, x.first, x.second, hipMemcpyDeviceToHost));
+    if (x.first) HIPCHK(net, copy_sync(net, out + off, x.first, x.second, hipMemcpyDeviceToHost));
+    else memset(out + off, 0, x.second);
     if (net->nd.n_pull && x.first == net->nd.acc)  // no input waits there but the next step's
       memset(out + off + (net->cur_step + 1) % kInBuf * (x.second / kInBuf), 0, x.second / kInBuf);
     off += x.second;
@@ -1097,8 +1135,11 @@ snn_status snn_restore(snn_net* net, const void* buf, size_t size) {
   HIPCHK(net, hipStreamSynchronize(net->stream));
   const char* in = static_cast<const char*>(buf);
   size_t off = sizeof h;
+  std::vector<int64_t> input;  // pulled: acc with what delivery through bins left in them
+  if (net->nd.n_pull) input = pull_waiting_input(net, in + off, h.cur_step);
   for (const auto& x : state_arrays(net)) {
-    HIPCHK(net, copy_sync(net, x.first, in + off, x.second, hipMemcpyHostToDevice));
+    const char* from = x.first == net->nd.acc && !input.empty() ? reinterpret_cast<const char*>(input.data()) : in + off;
+    if (x.first) HIPCHK(net, copy_sync(net, x.first, from, x.second, hipMemcpyHostToDevice));
     off += x.second;
   }
   if (net->nd.small_row) {  // the ring from the spikes in flight
@@ -1112,7 +1153,11 @@ snn_status snn_restore(snn_net* net, const void* buf, size_t size) {
     HIPCHK(net, hipStreamSynchronize(net->stream));
   }
   if (net->nd.n_pull) {  // the next step takes its input from acc
-    HIPCHK(net, launch_pull_restore(net->nd, (uint32_t)(h.cur_step % kInBuf), net->stream));
+    // a build of this network that delivers through bins adds acc where this is set
+    const std::vector<uint32_t> ones((size_t)kInBuf * net->nd.n_tiles, 1u);
+    HIPCHK(net, copy_sync(net, net->nd.ovf_flag, ones.data(), ones.size() * 4, hipMemcpyHostToDevice));
+    HIPCHK(net, hipMemsetAsync(net->nd.bin_cnt, 0, ones.size() * 4, net->stream));
+    HIPCHK(net, launch_pull_restore(net->nd, net->stream));
     HIPCHK(net, copy_sync(net, net->nd.pull_acc_step, &h.cur_step, 8, hipMemcpyHostToDevice));
     net->acc_step = h.cur_step;
   }
@@ -2380,6 +2425,8 @@ snn_status build_impl(snn_net* net) {
       nd.bins = d_bins; nd.bin_cnt = d_bcnt; nd.ovf_flag = d_bovf; nd.bin_off = d_boff; nd.bin_cap = d_bcap;
       nd.n_tiles = (uint32_t)nt; nd.tile_shift = tsh; nd.bins_total = tot;
       net->tile_neurons = T;
+      net->bin_off = std::move(off);
+      net->bin_cap = std::move(cap);
       // a batch of many small instances: consecutive spikes of a step belong to
       // one instance, whose targets lie in a few tiles, so delivery blocks take
       // contiguous item ranges from a queue (128 Brunel instances, 733 tiles:
@@ -2497,8 +2544,10 @@ snn_status build_impl(snn_net* net) {
   if (d_runs && !net->cfg.bin_capacity && !(net->cfg.tile_neurons && net->cfg.tile_neurons <= kPullTile) && !net->lean) {
     if ((st = build_pull(net, pop_cls))) return st;
   }
-  if (nd.n_pull) {
+  if (nd.n_pull) {  // no step reads a bin
     dev_free(net, d_runs);
+    dev_free(net, nd.bins);
+    nd.bins = nullptr;
     nd.tile_runs = 1;
   } else if (d_runs) {
     uint32_t* d_rd; ALLOC(d_rd, uint32_t, n_runs);

@@ -164,3 +164,18 @@ def test_extra_memory_keeps_no_request_waiting(snn):
         srv.close()
         for net in nets:
             net.close()
+
+
+def test_pulled_network_keeps_no_bins(snn):
+    """bins_total of a snapshot's header: 8 bytes each, two buffers, in the binned
+    network; the pulled one holds no such array."""
+    def sizes(**kw):
+        al = budget_allocator(snn, 1 << 40)
+        net = snn.Net(NETS["pull"][0](), allocator=al, delivery="binned", **kw)
+        total = int(net.snapshot()[32:40].view(np.uint64)[0])
+        out = net.step_kernel(), (8 * total + 255) // 256 * 256 in al.sizes.values()
+        net.close()
+        return out
+
+    assert sizes() == ("k_pull", False)
+    assert sizes(bin_capacity=100_000) == ("k_step_binned_runs", True)
