@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(kBT) k_bin_place(BinBuild bb, uint32_t D1, con
 // time are put in source order in LDS, so that a source's are written side by
 // side: placed at their (source, delay) groups at once, each by itself, 3.0 10^8
 // took 4.8 ms (every 4-byte store a line of its own), and the sorting of the
-// // groups, a wave each behind two dependent reads, another 2.7; now 1.1 here and
+// groups, a wave each behind two dependent reads, another 2.7; now 1.1 here and
 // 2.8 in k_row_sort.
 constexpr int kRowItems = 8;
 constexpr uint32_t kRowChunk = kRowItems * kBT;
@@ -530,29 +530,6 @@ constexpr int kRowSortRegs = 16;  // words of a row per thread of k_row_sort
 // 10^6 synapses in rows of 64: 2.66 and 2.85 ms; 1.3 10^7 of 128: 3.15, 3.11; 10^7
 // of 200: 2.30, 2.22)
 constexpr uint64_t kRowSortMean = 128;
-
-// Value of lane ^ j (j a power of two below 64, a constant once unrolled), by
-// moves between lanes in place of the LDS crossbar.
-template <int kCtrl>
-__device__ __forceinline__ uint32_t dpp(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, 0xf, 0xf, true);
-}
-__device__ __forceinline__ uint32_t lane_xor(uint32_t x, int j, uint32_t lane) {
-  switch (j) {
-    case 1: return dpp<0xb1>(x);              // quad_perm 1 0 3 2
-    case 2: return dpp<0x4e>(x);              // quad_perm 2 3 0 1
-    case 4: return dpp<0x1b>(dpp<0x141>(x));  // row_half_mirror (lane ^ 7), quad_perm 3 2 1 0 (lane ^ 3)
-    case 8: return dpp<0x128>(x);             // row_ror 8
-    case 16: {                                // odd rows of one copy against even rows of the other
-      const auto y = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-      return (lane & 16) ? y[0] : y[1];
-    }
-    default: {
-      const auto y = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-      return (lane & 32) ? y[0] : y[1];
-    }
-  }
-}
 
 template <int R>
 __device__ __forceinline__ void wave_sort(uint32_t* v, uint32_t lane) {

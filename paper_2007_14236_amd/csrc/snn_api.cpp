@@ -37,9 +37,9 @@ constexpr uint64_t kBinnedMinSynapses = 500000000;  // default delivery: binned 
 constexpr uint64_t kBinBuildMin = 1u << 20;        // build through bins of sources: synapses, at least
 constexpr uint64_t kBinBuildMax64 = 1ull << 31;    // ... at most (16 GiB of scratch)
 constexpr uint64_t kSmallSyn = 1u << 19;           // small networks: synapses, at most
+constexpr uint32_t kSmallPops = 16;                // ... and populations
 constexpr uint32_t kStripGrid = 256;               // strips, about
 constexpr uint64_t kStripFree = 64ull << 20;       // ... bytes of their index, and of their spill, not weighed
-constexpr uint32_t kSmallPops = 16;                // ... populations
 constexpr uint32_t kPullTile = 512;  // pulled delivery beyond tiles of this many neurons that were asked for
 constexpr uint32_t kPullUpd = 768;   // blocks of the pulled update that the chip holds at once
 constexpr uint64_t kPullMinMean = 4; // pulled delivery when the (group, tile) runs average this many synapses
@@ -1448,10 +1448,12 @@ uint32_t class_slots(const snn_net* net, const std::vector<std::vector<uint32_t>
 
 // A small LIF network (kernels_small.hip): one block runs all steps of a
 // launch.  The line: the ring of inputs fits one block's LDS, and the synapses
-// are few enough that a CU delivers a step's events no later than a launch per
-// step does at any rate (1,000 neurons in LDS: 876 events a step 2.2 us,
-// 16,800 events 6.8 us; by a launch per step 8.1 and 9.0 us; at a rate of a
-// spike per neuron and 2 ms, 2^19 synapses are 26,000 events a step).
+// are few enough that a CU delivers a step's events, at the highest rate that a
+// refractory time of 2 ms allows (26,000 a step of 2^19 synapses), no later than
+// device atomics in a launch per step.  Us a step in one block, by strips, by
+// atomics: 1,000 neurons and 880 events 2.2, 5.9, 8.2; 17,300 events 6.8, 8.3, 10.4;
+// two neurons a thread, 2,040 and 3,800 events 3.9, 5.9, 6.7; 17,600: 8.5, 6.4, 10.0;
+// 20,900: 9.6, 6.5, 11.8 (there alone, at 350 Hz and more, strips are faster).
 snn_status build_small(snn_net* net, const std::vector<std::vector<uint32_t>>& pop_cls) {
   const ExtraMemory extra(net);
   NetDev& nd = net->nd;
@@ -2384,13 +2386,16 @@ snn_status build_impl(snn_net* net) {
       return fail(net, SNN_E_UNSUPPORTED, "binned delivery: %llu tiles (at most %u) or %llu synapses onto one tile",
                   (unsigned long long)nt, kMaxTiles, (unsigned long long)max_in);
     net->tile_neurons = 0;
-    // default: binned for large networks, whose steps carry millions of events
-    // (10^6 AdEx neurons, 10^9 synapses: 190 us per step binned, 611 us direct;
-    // 128 Brunel instances, 8.7e9 synapses: 1.5 ms binned, 6.7 ms direct), and
-    // for every network with AdEx neurons, whose tile blocks feed the RK45 from
-    // a work queue (3e4-3e5 alpha-port neurons: 1.5x faster than direct); direct
-    // for smaller LIF networks, where the step is latency-bound (microcircuit
-    // stand-in, 3e8 synapses: 15 us direct, 24 us binned at its best tile size)
+    // default: binned for every network with AdEx neurons, whose tile blocks feed the
+    // RK45 from a work queue (3e4-3e5 alpha-port neurons: 1.5x faster than direct; 10^6
+    // AdEx neurons, 10^9 synapses: 190 us per step binned, 611 us direct), and for LIF
+    // networks of 5e8 synapses and more, which are mostly batches (128 Brunel instances,
+    // 8.7e9 synapses: 257 us pulled, 6.7 ms by atomics; ten of 25,000 neurons, 6.3e8
+    // synapses, at 230,000, 450,000 and 1.9e6 events a step: 33, 36, 41 us pulled, 17, 30,
+    // 105 by atomics: twenty populations are more than a strip's block holds).  Single LIF
+    // networks are faster by strips on both sides of the line: 77,000 neurons, 3.1e8, at
+    // 240,000 and 2.0e6 events: 8.4 and 29 us by strips, 28 and 35 pulled; 120,000, 6e8,
+    // at 240,000 and 1.0e6: 7.7 and 16, 29 and 32; 300,000, 6e8, at 750,000: 22, 52 binned
     const bool want = forced || (!(net->cfg.flags & SNN_F_DELIVERY_DIRECT) &&
                                  (total_syn >= kBinnedMinSynapses || net->has_adex));
     if (fits && want) {
