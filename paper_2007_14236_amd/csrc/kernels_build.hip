@@ -36,7 +36,7 @@
 // synapses (microcircuit stand-in): counting 11.1 and placing 23.4 ms by device
 // atomics; through bins drawing 5.2, counting 0.5 and placing 4.8 ms.  Below
 // 2^20 synapses the extra tables cost what the bins save (3 10^5: 0.76 against
-// 0.88 ms in all, 2.5 10^6: 1.32 against 0.97 ms).  Where a bin overflows
+// 0.88 ms in all, 2.5 10^6: 1.32 against 0.97 ms), and below 8 a neuron.  Where a bin overflows
 // (sources drawn far from uniformly) or the scratch does not fit, the atomics
 // do it.
 #include <algorithm>

@@ -35,6 +35,7 @@ constexpr int kNumParams = 16;  // SNN_P_TAU_M .. SNN_P_RK_HMIN
 constexpr uint64_t kChunkRing = 4096;  // >= drain interval + graph length
 constexpr uint64_t kBinnedMinSynapses = 500000000;  // default delivery: binned from this size on
 constexpr uint64_t kBinBuildMin = 1u << 20;        // build through bins of sources: synapses, at least
+constexpr uint64_t kBinBuildMean = 8;              // ... and for each neuron
 constexpr uint64_t kBinBuildMax64 = 1ull << 31;    // ... at most (16 GiB of scratch)
 constexpr uint64_t kSmallSyn = 1u << 19;           // small networks: synapses, at most
 constexpr uint32_t kSmallPops = 16;                // ... and populations
@@ -1660,13 +1661,16 @@ snn_status build_pull(snn_net* net, const std::vector<std::vector<uint32_t>>& po
 }
 
 // Bins of consecutive sources for the build (kernels_build.hip), planned by the
-// numbers of synapses that the rules expect.  bb.nbin stays 0 for small networks, sources that
-// do not fit the bins' counters, and where the scratch (8 bytes a synapse) is
-// too large or cannot be had; bufs: what was allocated.
+// numbers of synapses that the rules expect.  bb.nbin stays 0 for small networks,
+// for few synapses a neuron (the tables by neuron cost more than the bins save:
+// builds by device atomics and through bins, 2.4e6 neurons with one synapse 16.2
+// and 21.3 ms, 600,000 with 2 5.0 and 6.2, 400,000 with 6 4.7 and 4.7, 100,000 with
+// 12 1.9 and 1.8), for sources that do not fit the bins' counters, and where the
+// scratch (8 bytes a synapse) is too large or cannot be had; bufs: what was allocated.
 snn_status plan_bins(snn_net* net, uint64_t total_syn, uint32_t D1, BinBuild& bb, std::vector<void*>& bufs) {
   const ExtraMemory extra(net);
-  if (net->lean || total_syn < kBinBuildMin || total_syn > kBinBuildMax64) return SNN_OK;
   const uint32_t N = net->N;
+  if (net->lean || total_syn < kBinBuildMin || total_syn < kBinBuildMean * N || total_syn > kBinBuildMax64) return SNN_OK;
   std::map<uint32_t, double> step;  // expected synapses per source, its changes along the gids
   for (const HostProj& pr : net->projs) {
     if (!pr.synapses()) continue;

@@ -88,3 +88,11 @@ def test_targets_behind_two_kinds_of_sources(snn, na, ka, nb, kb):
     projs = [dict(src=s, tgt="T", K=k, weight=1.0, delay=("uniform", 0.1, 6.4), port=0) for s, k in (("A", ka), ("B", kb))]
     check(snn, dict(name="behind", dt=0.1, seed=4, dmax=63, populations=[pop("A", na), pop("B", nb), pop("T", 6000)],
                     projections=projs, poisson=[]))
+
+
+@pytest.mark.parametrize("k", [7, 9])
+def test_few_synapses_a_neuron(snn, k):
+    """160,000 sources of 7 synapses (drawn by device atomics) and of 9 (through bins)."""
+    pr = dict(src="S", tgt="T", rule="fixed_outdegree", K=k, weight=1.0, delay=("uniform", 0.1, 1.5), port=0)
+    check(snn, dict(name="few", dt=0.1, seed=4, dmax=15, populations=[pop("S", 160_000), pop("T", 100)], projections=[pr],
+                    poisson=[]))
