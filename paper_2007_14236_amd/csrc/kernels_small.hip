@@ -323,10 +323,10 @@ __global__ void __launch_bounds__(kB) k_small_poisson(NetDev nd, uint32_t steps)
 // acc[n & 1] (the other buffer cleared), and the pairs and events delivered so
 // far: those of every spike sent less those that arrive after step n.
 // Block 0: the counts; the others: the input.
-__global__ void __launch_bounds__(kB) k_small_fold(NetDev nd) {
+__global__ void __launch_bounds__(kT) k_small_fold(NetDev nd) {
   const uint64_t n = nd.ctrl->step_base;
   if (blockIdx.x > 0) {
-    const uint32_t i = (blockIdx.x - 1) * kB + threadIdx.x;
+    const uint32_t i = (blockIdx.x - 1) * kT + threadIdx.x;
     if (i >= nd.N) return;
     const uint32_t r = (uint32_t)(n % nd.R);
     int64_t a[kMaxPorts] = {0, 0, 0, 0};
@@ -340,9 +340,9 @@ __global__ void __launch_bounds__(kB) k_small_fold(NetDev nd) {
     }
     return;
   }
-  __shared__ uint64_t red[kB / 64];
+  __shared__ uint64_t red[kWaves];
   uint64_t ev, pr;
-  sent_pending<kB>(nd, n, ev, pr);
+  sent_pending<kT>(nd, n, ev, pr);
   ev = block_sum(ev, red);
   pr = block_sum(pr, red);
   if (threadIdx.x == 0) {
@@ -422,7 +422,7 @@ hipError_t launch_small_steps(const NetDev& nd, uint32_t steps, hipStream_t s, h
 }
 
 hipError_t launch_small_fold(const NetDev& nd, hipStream_t s) {
-  hipLaunchKernelGGL(k_small_fold, dim3(1 + (nd.N + kB - 1) / kB), dim3(kB), 0, s, nd);
+  hipLaunchKernelGGL(k_small_fold, dim3(1 + (nd.N + kT - 1) / kT), dim3(kT), 0, s, nd);
   return hipGetLastError();
 }
 

@@ -2722,8 +2722,7 @@ snn_status snn_get_counters(snn_net* net, snn_counters* out) {
   snn_status st = enter(net);
   if (st) return st;
   if ((net->nd.small_row || net->nd.n_strips) && (st = pull_fold(net))) return st;
-  HIPCHK(net, hipStreamSynchronize(net->stream));
-  Ctrl c;
+  Ctrl c;  // the copies wait for the stream
   HIPCHK(net, copy_sync(net, &c, net->nd.ctrl, sizeof c, hipMemcpyDeviceToHost));
   std::vector<uint64_t> ss((size_t)2 * net->nd.sel_grid);
   HIPCHK(net, copy_sync(net, ss.data(), net->nd.sel_stats, ss.size() * 8, hipMemcpyDeviceToHost));
